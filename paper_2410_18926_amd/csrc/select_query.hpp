@@ -238,6 +238,9 @@ __global__ __launch_bounds__(256) void k_select_query(QuerySelectArgs a) {
             }
             __syncthreads();
             count = s_count;
+            // every wavefront has read the counter before any adds the next chunk's arrivals to it: the block agrees
+            // on `count`, so on whether it compacts and on how many barriers that takes
+            if (p0 + kQChunk < m_c) __syncthreads();      // uniform
         }
         if (!overflow) compact();     // new scores arrived: raise the threshold before looking at the next cluster
     }
