@@ -232,8 +232,10 @@ int lorann_set_first_rows(lorann_index *ix, const float *first_row_A, const floa
  *   LORANN_RERANK_F16   a half-precision (IEEE binary16, round to nearest even) copy of it, half the bytes of the
  *                       step that dominates the search (Sec. 4.3: 16-bit floating point on the GPU).  Each stored
  *                       value is widened exactly and the arithmetic stays in float, so the result is the plain
- *                       re-rank over the rounded rows; candidates are unaffected.  The copy (2*n*d bytes) is made by
- *                       the first call that selects this mode and lives as long as the index.  LORANN_E_UNSUPPORTED
+ *                       re-rank over the rounded rows; candidates are unaffected.  The copy (rows padded to a
+ *                       multiple of 32 elements, 2 bytes each) is made when the index is loaded if it takes no more than
+ *                       a quarter of the GPU's free memory then, else by the first call that selects this mode, and
+ *                       lives as long as the index (the float mode screens its candidates with it).  LORANN_E_UNSUPPORTED
  *                       if a corpus value is not finite or exceeds 65504 in magnitude (mode unchanged).
  *   LORANN_RERANK_NONE  no re-ranking step (Sec. 7.1 memory usage, App. D.3): the k points of highest estimated
  *                       score are returned (ties at the boundary toward the lower corpus row), nearest first by

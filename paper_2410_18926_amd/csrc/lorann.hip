@@ -18,6 +18,7 @@
 #include "gemm_f64.hpp"
 #include "rerank.hpp"
 #include "rerank_group.hpp"
+#include "rerank_screen.hpp"
 #include "route.hpp"
 #include "score_mfma.hpp"
 #include "screen.hpp"
@@ -102,6 +103,7 @@ struct Workspace {
     DevBuf qproj, qbf, q8, dx, gscore, sel, count, rank_in_bucket, qrank, qorder, qorder2, off0, base_tab, bucket_off, tile_off, unit_off, slot_of_pos, pos_of_slot, Z, sigma, rho0, cand;
     DevBuf tau, n_kept, fb_list, pmax, voff, qkey, u_row, u_mask, u_pos, u_count, rdist, rcid, rccount;
     DevBuf smin, thr, hit_val, hit_grp, hit_cnt;      // screening without the matrix of approximate values
+    DevBuf qhalf, qstat, u_meta;                      // screened re-rank (its other lists share u_row, u_pos, u_count, rdist and rccount)
     hipStream_t stream = nullptr;          // lanes >= 1: created on first use, default priority
     hipEvent_t fork = nullptr, join = nullptr;
     hipEvent_t gather_done = nullptr;      // recorded after this lane's latest re-rank gather
@@ -110,7 +112,8 @@ struct Workspace {
     void release() {
         if (arena) return;
         DevBuf* bufs[] = {&qproj, &qbf, &q8, &dx, &gscore, &sel, &count, &rank_in_bucket, &qrank, &qorder, &qorder2, &off0, &base_tab, &bucket_off, &tile_off,
-                          &unit_off, &slot_of_pos, &pos_of_slot, &Z, &sigma, &rho0, &cand, &tau, &n_kept, &fb_list, &pmax, &voff, &qkey, &u_row, &u_mask, &u_pos, &u_count, &rdist, &rcid, &rccount};
+                          &unit_off, &slot_of_pos, &pos_of_slot, &Z, &sigma, &rho0, &cand, &tau, &n_kept, &fb_list, &pmax, &voff, &qkey, &u_row, &u_mask, &u_pos, &u_count, &rdist, &rcid, &rccount,
+                          &smin, &thr, &hit_val, &hit_grp, &hit_cnt, &qhalf, &qstat, &u_meta};
         for (DevBuf* b : bufs) b->release();
         if (fork) (void)hipEventDestroy(fork);
         if (gather_done) (void)hipEventDestroy(gather_done);
@@ -170,7 +173,9 @@ struct lorann_index {
     float* B_first = nullptr;       // [n]    ... and of every B_c (one value per point)
     int64_t* off = nullptr;         // [L+1]
     float* corpus = nullptr;        // [n][d]
-    _Float16* corpus_h = nullptr;   // [n][d] binary16 copy, made when the half-precision re-rank is first selected
+    _Float16* corpus_h = nullptr;   // [n][ld_h] binary16 copy of the corpus (NULL: it does not fit, or binary16 cannot hold the values)
+    int32_t ld_h = 0;               // its row stride
+    HalfStats half{};               // what the copy lost
     int32_t rerank_mode = LORANN_RERANK_F32;
     int64_t* ids = nullptr;         // [n] or NULL
     float* sqnorm = nullptr;        // [n] (Euclidean)
@@ -214,6 +219,40 @@ int dev_copy(T** dst, const T* src, size_t count) {
     HIP_TRY(hipMalloc(reinterpret_cast<void**>(dst), std::max<size_t>(count, 1) * sizeof(T)));
     if (count) HIP_TRY(hipMemcpy(*dst, src, count * sizeof(T), hipMemcpyDefault));
     return LORANN_OK;
+}
+
+// The binary16 copy of the corpus and the statistics of its rounding.  required: report why it cannot be made (the
+// half-precision re-rank was asked for); otherwise the index goes without - as it does when the copy would take more than a quarter
+// of the memory that is free (a corpus that fills most of the GPU must still load, and the caller needs room beside it).
+int make_half_corpus(lorann_index* ix, bool required) {
+    if (ix->corpus_h) return LORANN_OK;
+    const int ld = half_stride(ix->d);
+    const size_t bytes = (size_t)ix->n * ld * sizeof(_Float16);
+    if (!required) {
+        size_t free_b = 0, total_b = 0;
+        if (hipMemGetInfo(&free_b, &total_b) != hipSuccess) { (void)hipGetLastError(); return LORANN_OK; }
+        if (bytes > free_b / 4) return LORANN_OK;
+    }
+    _Float16* h = nullptr;
+    uint32_t* st = nullptr;
+    hipError_t e = hipMalloc((void**)&h, bytes);
+    if (e == hipSuccess) e = hipMalloc((void**)&st, sizeof(HalfStats));
+    if (e == hipSuccess) e = hipMemset(st, 0, sizeof(HalfStats));
+    if (e == hipSuccess) {
+        const unsigned grid = (unsigned)std::min<int64_t>((ix->n + 3) / 4, 2048);
+        hipLaunchKernelGGL(k_corpus_to_half_rows, dim3(grid), dim3(256), 0, nullptr, ix->corpus, h, ix->n, ix->d, ld, st);
+        e = hipGetLastError();
+    }
+    HalfStats hs{};
+    if (e == hipSuccess) e = hipMemcpy(&hs, st, sizeof hs, hipMemcpyDeviceToHost);
+    if (st) (void)hipFree(st);
+    const bool holds = e == hipSuccess && hs.abs_max <= 65504.0f;
+    if (holds) { ix->corpus_h = h; ix->ld_h = ld; ix->half = hs; return LORANN_OK; }
+    if (h) (void)hipFree(h);
+    (void)hipGetLastError();
+    if (!required) return LORANN_OK;
+    if (e != hipSuccess) return fail(e == hipErrorOutOfMemory ? LORANN_E_NOMEM : LORANN_E_DEVICE, "building the half-precision corpus failed: %s", hipGetErrorString(e));
+    return fail(LORANN_E_UNSUPPORTED, "the corpus holds values beyond the binary16 range (largest magnitude %g)", (double)hs.abs_max);
 }
 
 __global__ void k_pad_codes(const int8_t* __restrict__ B, int8_t* __restrict__ Bp, int64_t n, int r, int r_pad) {
@@ -315,6 +354,10 @@ void launch_pair_max(lorann_index* ix, Workspace& ws, hipStream_t s, int64_t npa
 // What one batch will run, decided before anything is enqueued.
 struct ChunkPlan {
     bool mixed, screen, fused_quant, big_matrix, lds_hist, grouped;
+    bool handful;       // up to 8 queries: distances and top-k of the re-rank in one launch
+    bool screened;      // re-rank screened by the binary16 copy of the corpus
+    int screen_gq;      // queries per group of the screened re-rank
+    int screen_stride;  // list entries per group
     bool small;         // query-major path of small batches (no bucketing)
     bool digest;        // screening from subset minima and hit lists: the matrix of approximate values is never written
     int group_q;        // queries per re-rank group (0: rows too long to share)
@@ -322,7 +365,7 @@ struct ChunkPlan {
     int64_t ngroups;
 };
 
-ChunkPlan plan_chunk(const lorann_index* ix, int64_t nq, int w, int m) {
+ChunkPlan plan_chunk(const lorann_index* ix, int64_t nq, int k, int w, int m, bool allow_screened = true) {
     ChunkPlan pl;
     const int L = ix->L;
     pl.mixed = ix->A_first != nullptr;      // Sec. 4.2: first component of q' and of every r stay in float
@@ -348,8 +391,18 @@ ChunkPlan plan_chunk(const lorann_index* ix, int64_t nq, int w, int m) {
     // A few dozen queries: hardly two pairs share a cluster, so the pairs stay in slot order and every launch that only
     // serves the bucketing is left out (per-cluster step sizes only).
     pl.small = nq <= kSmallPathQueries && pl.screen && !pl.mixed && ix->sA_cols == nullptr && ix->rerank_mode != LORANN_RERANK_NONE;
+    pl.handful = pl.small && pl.grouped && nq <= 8 && ix->d % 4 == 0 && ix->d <= 1024 && k <= 64;
+    // The screened re-rank reads all candidates at half width and about k of them in full: it pays while k is a small part of m
+    // (a row read at half width is shared by about two queries, one read in full is not, so up to k = m / 4).  A few dozen queries are
+    // bound by the latency of the three launches, where the grouped re-rank's are shorter (64 queries: 115 us against 118).
+    const int ld = half_stride(ix->d);
+    pl.screen_gq = std::min(pl.small ? 1 : screen_group_size(m), (64 * 1024) / (2 * ld + 16));
+    pl.screened = allow_screened && ix->rerank_mode != LORANN_RERANK_NONE && !ix->force_exact && !(pl.small && pl.grouped) && ix->corpus_h && pl.screen_gq > 0 && 4 * k <= m;
+    pl.screen_stride = (pl.screen_gq * m + 15) & ~15;
+    if (pl.screened) pl.grouped = false;
     // (small batches: a group per query - nothing to share, and the union and the gather of a group are latency chains)
-    pl.ngroups = !pl.grouped ? 0 : pl.small ? nq : (nq + pl.group_q - 1) / pl.group_q;
+    const int gq = pl.screened ? pl.screen_gq : pl.small ? 1 : pl.group_q;
+    pl.ngroups = !pl.grouped && !pl.screened ? 0 : (nq + gq - 1) / gq;
     return pl;
 }
 
@@ -361,7 +414,7 @@ int reserve_workspace(const lorann_index* ix, Workspace& ws, const ChunkPlan& pl
     Arena* ar = ws.arena;
     if (ar) ar->used = 0;
     struct Want { DevBuf* b; size_t bytes; bool on; };
-    const size_t gm = (size_t)pl.group_q * m;
+    const size_t gm = (size_t)pl.group_q * m, sgroups = (size_t)pl.ngroups * pl.screen_stride;
     const bool no_rerank = ix->rerank_mode == LORANN_RERANK_NONE;
     const Want wants[] = {
         {&ws.qproj, q * dp * 4, true}, {&ws.q8, q * dp, true}, {&ws.dx, q * 4, true}, {&ws.gscore, q * L * 4, true},
@@ -376,7 +429,10 @@ int reserve_workspace(const lorann_index* ix, Workspace& ws, const ChunkPlan& pl
         {&ws.tau, q * 4, !ix->force_exact}, {&ws.n_kept, q * 4, !ix->force_exact}, {&ws.fb_list, q * 4, !ix->force_exact},
         {&ws.qkey, q * 4, !ix->force_exact},
         {&ws.u_row, (size_t)pl.ngroups * gm * 4, pl.grouped}, {&ws.u_mask, (size_t)pl.ngroups * gm * 2, pl.grouped},
-        {&ws.u_pos, (size_t)pl.ngroups * gm * pl.group_q * 2, pl.grouped}, {&ws.u_count, (size_t)pl.ngroups * 4, pl.grouped},
+        {&ws.u_pos, (size_t)pl.ngroups * gm * pl.group_q * 2, pl.grouped}, {&ws.u_count, (size_t)pl.ngroups * 4, pl.grouped || pl.screened},
+        {&ws.u_row, sgroups * 4, pl.screened}, {&ws.u_meta, sgroups * 4, pl.screened}, {&ws.u_pos, q * m * 2, pl.screened}, {&ws.rccount, q * 4, pl.screened && !pl.small},
+        {&ws.qhalf, (size_t)pl.ngroups * pl.screen_gq * half_stride(ix->d) * 2, pl.screened}, {&ws.qstat, q * 16, pl.screened},
+        {&ws.rdist, sgroups * (ix->metric == LORANN_L2 ? 8 : 4), pl.screened},
         {&ws.rdist, q * m * 4, pl.grouped || no_rerank}, {&ws.rcid, q * m * 8, pl.grouped || no_rerank},
         {&ws.rccount, q * 4, pl.grouped || no_rerank || pl.small},      // (small batches: also the tickets of the one-launch re-rank)
         {&ws.smin, q * kFusedSubsets * 4, pl.digest}, {&ws.thr, q * 4, pl.digest},
@@ -397,13 +453,88 @@ int reserve_workspace(const lorann_index* ix, Workspace& ws, const ChunkPlan& pl
     return LORANN_OK;
 }
 
+// The plan of a batch and its buffers.  A search that fits the fixed region only without the screened re-rank's lists goes without.
+int plan_and_reserve(const lorann_index* ix, Workspace& ws, int64_t nq, int k, int w, int m, ChunkPlan& pl) {
+    pl = plan_chunk(ix, nq, k, w, m);
+    int rc = reserve_workspace(ix, ws, pl, nq, w, m);
+    if (rc == LORANN_E_UNSUPPORTED && ws.arena && pl.screened) {
+        pl = plan_chunk(ix, nq, k, w, m, false);
+        rc = reserve_workspace(ix, ws, pl, nq, w, m);
+    }
+    return rc;
+}
+
+// The screened re-rank of one batch: union, matrix-core gather over the binary16 rows, exact finish.
+template <typename B, typename E>
+int launch_screened_rerank(lorann_index* ix, Workspace& ws, hipStream_t s, const ChunkPlan& pl, const float* dQ, int64_t nq, int k, int m,
+                           int64_t* d_ids, float* d_dists, B turn_begin, E turn_end) {
+    const bool half_rows = ix->rerank_mode == LORANN_RERANK_F16, l2 = ix->metric == LORANN_L2;
+    const HalfStats& hs = ix->half;
+    const int d = ix->d;
+    ScreenRerankArgs ra{};
+    ra.Q = dQ; ra.corpus = half_rows ? (const void*)ix->corpus_h : (const void*)ix->corpus; ra.half = ix->corpus_h; ra.sqnorm = ix->sqnorm; ra.ids = ix->ids;
+    ra.cand = ws.cand.as<int32_t>(); ra.qorder = pl.small ? ws.qorder.as<int32_t>() : ws.qorder2.as<int32_t>();
+    ra.qhalf = ws.qhalf.as<_Float16>(); ra.qstat = ws.qstat.as<float4>(); ra.u_row = ws.u_row.as<int32_t>(); ra.u_meta = ws.u_meta.as<uint32_t>();
+    ra.entry = ws.u_pos.as<uint16_t>(); ra.qgroup = ws.rccount.as<int32_t>(); ra.u_count = ws.u_count.as<int32_t>(); ra.approx = ws.rdist.as<float>(); ra.out_ids = d_ids; ra.out_dists = d_dists;
+    ra.nq = (int)nq; ra.d = d; ra.ld = ix->ld_h; ra.m = m; ra.k = k; ra.gq = pl.screen_gq; ra.gstride = pl.screen_stride; ra.metric = ix->metric;
+    // (rounded up; half rows: the stored row is what counts, only the subnormal elements may be lost to the matrix core)
+    ra.norm = (half_rows ? hs.norm + hs.err : hs.norm) * 1.0001f;
+    ra.err = (half_rows ? hs.lost : hs.err) * 1.0001f;
+    ra.rel_err = (half_rows ? hs.rel_lost : hs.rel_err) * 1.0001f;
+    ra.rel_norm = half_rows ? 1.0001f * hs.rel_round * (2.0f + hs.rel_round) : 0.0f;
+    ra.nscale = half_rows ? 1.0001f * (1.0f + hs.rel_round) : 1.0001f;
+    // blocks of a few tiles per wavefront: enough of them to fill the machine several times over
+    ra.slices = 1;
+    const int max_slices = std::min(16, (pl.screen_gq * m + 63) / 64);
+    while ((int64_t)ra.slices * pl.ngroups < 4096 && ra.slices < max_slices) ++ra.slices;
+    ws.last_ngroups = pl.ngroups;
+    {
+        Prof p(ix, K_UNION, s);
+        hipLaunchKernelGGL(k_screen_union, dim3((unsigned)pl.ngroups), dim3(kScreenUnionThreads), pl.screen_gq > 1 ? (size_t)kScreenSlots * 8 : 0, s, ra);
+    }
+    { const int rc = turn_begin(); if (rc) return rc; }
+    {
+        Prof p(ix, K_RERANK, s);
+        const dim3 grid((unsigned)(pl.ngroups * ra.slices));
+        const size_t lds = (size_t)pl.screen_gq * (2 * ix->ld_h + 16);
+        if (l2) hipLaunchKernelGGL(k_screen_gather<true>, grid, dim3(256), lds, s, ra);
+        else hipLaunchKernelGGL(k_screen_gather<false>, grid, dim3(256), lds, s, ra);
+    }
+    {
+        Prof p(ix, K_TOPK, s);
+        const int nv = d <= 1024 ? (d + 255) / 256 : 0;
+#define LAUNCH_SF5(L2_, NV_, V_, T_, NW_, EPL_) hipLaunchKernelGGL((k_screen_finish<L2_, NV_, V_, T_, NW_, EPL_>), dim3((unsigned)((nq * NW_ + 3) / 4)), dim3(256), (size_t)(4 / NW_) * 64 * NW_ * EPL_ * 12, s, ra)
+#define LAUNCH_SF4(L2_, NV_, T_, NW_, EPL_) do { if (d % 4 == 0 || NV_ == 0) LAUNCH_SF5(L2_, NV_, true, T_, NW_, EPL_); else LAUNCH_SF5(L2_, NV_, (NV_ == 0), T_, NW_, EPL_); } while (0)
+#define LAUNCH_SF3(L2_, NV_, T_) do { if (m <= 256) LAUNCH_SF4(L2_, NV_, T_, 1, 4); else if (m <= 512) LAUNCH_SF4(L2_, NV_, T_, 1, 8); \
+                                      else if (m <= 1024) LAUNCH_SF4(L2_, NV_, T_, 4, 4); else LAUNCH_SF4(L2_, 0, T_, 4, 16); } while (0)
+#define LAUNCH_SF2(L2_, NV_) do { if (half_rows) LAUNCH_SF3(L2_, NV_, _Float16); else LAUNCH_SF3(L2_, NV_, float); } while (0)
+#define LAUNCH_SF(L2_)                                                                                         \
+    do {                                                                                                       \
+        switch (nv) {                                                                                          \
+            case 1: LAUNCH_SF2(L2_, 1); break;                                                                 \
+            case 2: LAUNCH_SF2(L2_, 2); break;                                                                 \
+            case 3: LAUNCH_SF2(L2_, 3); break;                                                                 \
+            case 4: LAUNCH_SF2(L2_, 4); break;                                                                 \
+            default: LAUNCH_SF2(L2_, 0); break;                                                                \
+        }                                                                                                      \
+    } while (0)
+        if (l2) LAUNCH_SF(true); else LAUNCH_SF(false);
+#undef LAUNCH_SF
+#undef LAUNCH_SF2
+#undef LAUNCH_SF3
+#undef LAUNCH_SF4
+#undef LAUNCH_SF5
+    }
+    return turn_end();
+}
+
 // One batch of at most `chunk` queries, device pointers only.
 int search_chunk(lorann_index* ix, Workspace& ws, hipStream_t s, const float* dQ, int64_t nq, int k, int w, int m, int64_t* d_ids,
                  float* d_dists, const lorann_stages* st, int64_t q_base, int32_t* fb_total) {
     const int L = ix->L, dp = ix->dp, d = ix->d, r_pad = ix->r_pad;
     const int64_t npairs = nq * w;
-    const ChunkPlan pl = plan_chunk(ix, nq, w, m);
-    { const int rc = reserve_workspace(ix, ws, pl, nq, w, m); if (rc) return rc; }
+    ChunkPlan pl;
+    { const int rc = plan_and_reserve(ix, ws, nq, k, w, m, pl); if (rc) return rc; }
     const bool mixed = pl.mixed;
 
     const float* qp = dQ;   // projected queries
@@ -625,7 +756,7 @@ int search_chunk(lorann_index* ix, Workspace& ws, hipStream_t s, const float* dQ
         }
         sa_.qlist = ws.fb_list.as<int32_t>(); sa_.qcount = ws.count.as<int32_t>() + 2 * L;
         sa_.fb_total = fb_total;      // asynchronous searches being profiled: the count is added up on the device
-        if (!grouped && !pl.small) {  // (the grouped re-rank finishes these queries in the launch that orders the queries; small batches inline)
+        if (!grouped && !pl.screened && !pl.small) {  // (the grouped and the screened re-rank finish these queries in the launch that orders the queries; small batches inline)
             Prof p(ix, K_SELECT_M, s);
             const unsigned grid = (unsigned)std::min<int64_t>(nq, 1024);
             if (r_pad == 32) hipLaunchKernelGGL(k_select_exact<2>, dim3(grid), dim3(256), 0, s, sa_, (int)nq);
@@ -634,6 +765,7 @@ int search_chunk(lorann_index* ix, Workspace& ws, hipStream_t s, const float* dQ
     }
     const int mp2 = std::max(256, next_pow2(m));
     const bool half_rows = ix->rerank_mode == LORANN_RERANK_F16;
+    const int ld_rows = half_rows ? ix->ld_h : d;
     if (ix->rerank_mode == LORANN_RERANK_NONE) {
         // no re-ranking step: the candidates (m == k here) are the answer, ordered by their estimated scores
         sa_.qlist = nullptr; sa_.qcount = nullptr; sa_.fb_total = nullptr;
@@ -645,14 +777,14 @@ int search_chunk(lorann_index* ix, Workspace& ws, hipStream_t s, const float* dQ
         }
         GroupArgs ga{};
         ga.dist = ws.rdist.as<float>(); ga.cid = ws.rcid.as<int64_t>(); ga.ccount = ws.rccount.as<int32_t>();
-        ga.out_ids = d_ids; ga.out_dists = d_dists; ga.nq = (int)nq; ga.d = d; ga.m = m; ga.k = k;
+        ga.out_ids = d_ids; ga.out_dists = d_dists; ga.nq = (int)nq; ga.d = d; ga.ld = ld_rows; ga.m = m; ga.k = k;
         {
             Prof p(ix, K_TOPK, s);
             if (k <= 64) hipLaunchKernelGGL(k_topk_wave<4>, dim3((unsigned)((nq + 3) / 4)), dim3(256), 0, s, ga);
             else hipLaunchKernelGGL(k_topk, dim3((unsigned)nq), dim3(256), (size_t)mp2 * 12, s, ga, mp2);
         }
-    } else if (grouped) {
-        // grouped re-rank: neighbours in the visiting order share candidate rows, each distinct row is gathered once
+    } else if (grouped || pl.screened) {
+        // neighbours in the visiting order share candidate rows, each distinct row is read once per group of queries
         if (!pl.small) {          // (small batches: no overflow list to finish, and the queries keep their given order)
             Prof p(ix, K_ORDER, s);
             const int fb_blocks = (int)std::min<int64_t>(nq, 1024);
@@ -660,14 +792,31 @@ int search_chunk(lorann_index* ix, Workspace& ws, hipStream_t s, const float* dQ
             if (r_pad == 32) hipLaunchKernelGGL(k_finish_and_order<2>, grid, dim3(256), 0, s, sa_, fb_blocks, ws.qorder.as<int32_t>(), ws.off0.as<int32_t>(), L, (int)nq, ws.qkey.as<int32_t>(), ws.qorder2.as<int32_t>());
             else hipLaunchKernelGGL(k_finish_and_order<4>, grid, dim3(256), 0, s, sa_, fb_blocks, ws.qorder.as<int32_t>(), ws.off0.as<int32_t>(), L, (int)nq, ws.qkey.as<int32_t>(), ws.qorder2.as<int32_t>());
         }
-        if (pl.small && nq <= 8 && d % 4 == 0 && d <= 1024 && k <= 64) {
+        // The gathers of different lanes take turns: each alone saturates HBM, so two at once only stretch each other,
+        // while the other stages of the other lanes still run beside a gather.
+        const bool turns = ix->gather_turns != 0 && !ws.arena && !pl.handful;      // (creating the turn's event is an allocation)
+        auto turn_begin = [&]() -> int {
+            if (turns && ix->last_gather && ix->last_gather != ws.gather_done) HIP_TRY(hipStreamWaitEvent(s, ix->last_gather, 0));
+            return LORANN_OK;
+        };
+        auto turn_end = [&]() -> int {
+            if (!turns) return LORANN_OK;
+            if (!ws.gather_done) HIP_TRY(hipEventCreateWithFlags(&ws.gather_done, hipEventDisableTiming));
+            HIP_TRY(hipEventRecord(ws.gather_done, s));
+            ix->last_gather = ws.gather_done;
+            return LORANN_OK;
+        };
+        if (pl.screened) {
+            const int rc = launch_screened_rerank(ix, ws, s, pl, dQ, nq, k, m, d_ids, d_dists, turn_begin, turn_end);
+            if (rc) return rc;
+        } else if (pl.handful) {
             // a handful of queries: no union (a query's candidates are distinct rows), distances and top-k in one launch
             // (its per-block device-scope fences cost more than the two launches they save from a few hundred blocks on:
             // measured 106 us against 31 us at 64 queries)
             GroupArgs ga{};
             ga.Q = dQ; ga.corpus = half_rows ? (const void*)ix->corpus_h : (const void*)ix->corpus; ga.ids = ix->ids; ga.cand = ws.cand.as<int32_t>();
             ga.dist = ws.rdist.as<float>(); ga.cid = ws.rcid.as<int64_t>(); ga.ccount = ws.rccount.as<int32_t>();
-            ga.out_ids = d_ids; ga.out_dists = d_dists; ga.nq = (int)nq; ga.d = d; ga.m = m; ga.k = k;
+            ga.out_ids = d_ids; ga.out_dists = d_dists; ga.nq = (int)nq; ga.d = d; ga.ld = ld_rows; ga.m = m; ga.k = k;
             ws.last_ngroups = 0;
             const int slices = std::min(16, (m + 7) / 8);
             const int nv = (d / 4 + 63) / 64;
@@ -698,7 +847,7 @@ int search_chunk(lorann_index* ix, Workspace& ws, hipStream_t s, const float* dQ
         ga.Q = dQ; ga.corpus = half_rows ? (const void*)ix->corpus_h : (const void*)ix->corpus; ga.ids = ix->ids; ga.cand = ws.cand.as<int32_t>(); ga.qorder = pl.small ? ws.qorder.as<int32_t>() : ws.qorder2.as<int32_t>();
         ga.u_row = ws.u_row.as<int32_t>(); ga.u_mask = ws.u_mask.as<uint16_t>(); ga.u_pos = ws.u_pos.as<uint16_t>(); ga.u_count = ws.u_count.as<int32_t>();
         ga.dist = ws.rdist.as<float>(); ga.cid = ws.rcid.as<int64_t>(); ga.ccount = ws.rccount.as<int32_t>();
-        ga.out_ids = d_ids; ga.out_dists = d_dists; ga.nq = (int)nq; ga.d = d; ga.m = m; ga.k = k;
+        ga.out_ids = d_ids; ga.out_dists = d_dists; ga.nq = (int)nq; ga.d = d; ga.ld = ld_rows; ga.m = m; ga.k = k;
         ga.gq = pl.small ? 1 : kGroupQ;
         ga.ht = rerank_group_ht(ga.gq, m);
         ws.last_ngroups = ngroups;
@@ -709,10 +858,7 @@ int search_chunk(lorann_index* ix, Workspace& ws, hipStream_t s, const float* dQ
             Prof p(ix, K_UNION, s);
             hipLaunchKernelGGL(k_group_union<8>, dim3((unsigned)ngroups), dim3(kUnionThreads), (size_t)ga.ht * 6, s, ga);
         }
-        // The gathers of different lanes take turns: each alone saturates HBM, so two at once only stretch each other,
-        // while the other stages of the other lanes still run beside a gather.
-        const bool turns = ix->gather_turns != 0 && !ws.arena;      // (creating the turn's event is an allocation)
-        if (turns && ix->last_gather && ix->last_gather != ws.gather_done) HIP_TRY(hipStreamWaitEvent(s, ix->last_gather, 0));
+        { const int rc = turn_begin(); if (rc) return rc; }
         {
             Prof p(ix, K_RERANK, s);
             const dim3 grid((unsigned)(ngroups * ga.slices));
@@ -739,11 +885,7 @@ int search_chunk(lorann_index* ix, Workspace& ws, hipStream_t s, const float* dQ
 #undef LAUNCH_GG3
 #undef LAUNCH_GG
         }
-        if (turns) {
-            if (!ws.gather_done) HIP_TRY(hipEventCreateWithFlags(&ws.gather_done, hipEventDisableTiming));
-            HIP_TRY(hipEventRecord(ws.gather_done, s));
-            ix->last_gather = ws.gather_done;
-        }
+        { const int rc = turn_end(); if (rc) return rc; }
         {
             Prof p(ix, K_TOPK, s);
             if (k <= 64 && m <= 256) hipLaunchKernelGGL(k_topk_wave<4>, dim3((unsigned)((nq + 3) / 4)), dim3(256), 0, s, ga);
@@ -758,8 +900,8 @@ int search_chunk(lorann_index* ix, Workspace& ws, hipStream_t s, const float* dQ
         const dim3 rgrid((unsigned)(8 * ((nq + 7) / 8)));
 #define LAUNCH_RR(M_)                                                                                          \
     do {                                                                                                       \
-        if (half_rows) hipLaunchKernelGGL((k_rerank<M_, _Float16>), rgrid, dim3(256), lds, s, dQ, (const _Float16*)ix->corpus_h, ix->ids, cand, ws.qorder.as<int32_t>(), (int)nq, d, m, mp2, k, d_ids, d_dists); \
-        else hipLaunchKernelGGL((k_rerank<M_, float>), rgrid, dim3(256), lds, s, dQ, (const float*)ix->corpus, ix->ids, cand, ws.qorder.as<int32_t>(), (int)nq, d, m, mp2, k, d_ids, d_dists); \
+        if (half_rows) hipLaunchKernelGGL((k_rerank<M_, _Float16>), rgrid, dim3(256), lds, s, dQ, (const _Float16*)ix->corpus_h, ix->ids, cand, ws.qorder.as<int32_t>(), (int)nq, d, ld_rows, m, mp2, k, d_ids, d_dists); \
+        else hipLaunchKernelGGL((k_rerank<M_, float>), rgrid, dim3(256), lds, s, dQ, (const float*)ix->corpus, ix->ids, cand, ws.qorder.as<int32_t>(), (int)nq, d, ld_rows, m, mp2, k, d_ids, d_dists); \
     } while (0)
         if (ix->metric == LORANN_IP) LAUNCH_RR(0);
         else if (ix->metric == LORANN_L2) LAUNCH_RR(1);
@@ -893,8 +1035,8 @@ int search_impl(lorann_index* ix, const float* queries, int64_t nq, int32_t k, i
         HIP_TRY(hipGetDevice(&cur));
         if (cur != ix->device) return fail(LORANN_E_INVAL, "the index lives on device %d, the current device is %d", ix->device, cur);
         const int64_t cn = std::min(chunk, nq);
-        const ChunkPlan pl = plan_chunk(ix, cn, w, m);
-        if ((rc0 = reserve_workspace(ix, ws, pl, cn, w, m))) return rc0;
+        ChunkPlan pl;
+        if ((rc0 = plan_and_reserve(ix, ws, cn, k, w, m, pl))) return rc0;
     }
     if (lane > 0) {     // the lane starts after what the index's stream holds now (the caller's queries)
         HIP_TRY(hipEventRecord(ws.fork, ix->stream));
@@ -1082,6 +1224,7 @@ int lorann_load_index(lorann_index** out, int32_t metric, int64_t n, int32_t d, 
             hipLaunchKernelGGL(k_row_sqnorm<float>, dim3((unsigned)((n + 3) / 4)), dim3(256), 0, 0, ix->corpus, ix->sqnorm, n, d);
             HIP_TRY(hipDeviceSynchronize());
         }
+        if ((e = make_half_corpus(ix, false))) return e;
         return LORANN_OK;
     };
     rc = body();
@@ -1252,26 +1395,7 @@ int lorann_set_rerank(lorann_index* ix, int32_t mode) {
     if (!ix) return fail(LORANN_E_INVAL, "index is NULL");
     if (mode != LORANN_RERANK_F32 && mode != LORANN_RERANK_F16 && mode != LORANN_RERANK_NONE) return fail(LORANN_E_INVAL, "unknown re-rank mode %d", mode);
     { const int rc = sync_all(ix); if (rc) return rc; }   // searches in flight keep the mode they were enqueued with
-    if (mode == LORANN_RERANK_F16 && !ix->corpus_h) {
-        const size_t count = (size_t)ix->n * ix->d;
-        _Float16* h = nullptr;
-        uint32_t* mx = nullptr;
-        HIP_TRY(hipMalloc((void**)&h, count * 2));
-        hipError_t e = hipMalloc((void**)&mx, 4);
-        if (e == hipSuccess) e = hipMemset(mx, 0, 4);
-        uint32_t bits = 0;
-        if (e == hipSuccess) {
-            const unsigned grid = (unsigned)std::min<size_t>((count + 255) / 256, 16384);
-            hipLaunchKernelGGL(k_corpus_to_half, dim3(grid), dim3(256), 0, nullptr, ix->corpus, h, count, mx);
-            e = hipGetLastError();
-        }
-        if (e == hipSuccess) e = hipMemcpy(&bits, mx, 4, hipMemcpyDeviceToHost);
-        if (mx) (void)hipFree(mx);
-        if (e != hipSuccess) { (void)hipFree(h); (void)hipGetLastError(); return fail(e == hipErrorOutOfMemory ? LORANN_E_NOMEM : LORANN_E_DEVICE, "building the half-precision corpus failed: %s", hipGetErrorString(e)); }
-        float mxf; memcpy(&mxf, &bits, 4);
-        if (!(mxf <= 65504.0f)) { (void)hipFree(h); return fail(LORANN_E_UNSUPPORTED, "the corpus holds values beyond the binary16 range (largest magnitude %g)", (double)mxf); }
-        ix->corpus_h = h;
-    }
+    if (mode == LORANN_RERANK_F16) { const int rc = make_half_corpus(ix, true); if (rc) return rc; }
     ix->rerank_mode = mode;
     return LORANN_OK;
 }

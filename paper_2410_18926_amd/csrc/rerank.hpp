@@ -36,28 +36,12 @@ __device__ __forceinline__ f16x4 row_load(const f16x4* p) {
     return __builtin_nontemporal_load(p);
 }
 
-// The half-precision copy of the corpus: round to nearest even.  *max_abs_bits receives the largest |x| seen (as
-// float bits; a NaN compares above everything) so that the host can refuse rows binary16 cannot hold.
-// grid-stride over count elements, block = 256.
-__global__ __launch_bounds__(256) void k_corpus_to_half(const float* __restrict__ src, _Float16* __restrict__ dst, size_t count,
-                                                         uint32_t* __restrict__ max_abs_bits) {
-    uint32_t mx = 0u;
-    for (size_t i = (size_t)blockIdx.x * 256 + threadIdx.x; i < count; i += (size_t)gridDim.x * 256) {
-        const float v = src[i];
-        mx = max(mx, __float_as_uint(v) & 0x7fffffffu);
-        dst[i] = (_Float16)v;
-    }
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) mx = max(mx, (uint32_t)__shfl_xor((int)mx, o, 64));
-    if ((threadIdx.x & 63) == 0) atomicMax(max_abs_bits, mx);
-}
-
 __device__ __forceinline__ bool rr_less(float da, int64_t ia, float db, int64_t ib) {
     return da < db || (da == db && ia < ib);
 }
 
 // grid = 8 * ceil(nq / 8), block = 256, dynamic LDS = d*4 + mp2*(4 + 8) bytes (mp2 = power of two >= m, >= 256).
-// METRIC: 0 inner product, 1 squared Euclidean, 2 cosine.
+// METRIC: 0 inner product, 1 squared Euclidean, 2 cosine.  ld = elements from one stored row to the next.
 // Queries are taken in the order of `qorder` (grouped by nearest cluster: queries that share candidates run at
 // the same time, so a corpus row gathered for one of them is still in cache for the others), and consecutive
 // entries of that order go to the same XCD (workgroups are dealt round-robin over the 8 XCDs, each with its own L2).
@@ -65,7 +49,7 @@ template <int METRIC, typename T>
 __global__ __launch_bounds__(256) void k_rerank(const float* __restrict__ Q, const T* __restrict__ corpus,
                                                  const int64_t* __restrict__ ids, const int32_t* __restrict__ cand,
                                                  const int32_t* __restrict__ qorder, int nq,
-                                                 int d, int m, int mp2, int k, int64_t* __restrict__ out_ids,
+                                                 int d, int ld, int m, int mp2, int k, int64_t* __restrict__ out_ids,
                                                  float* __restrict__ out_dists) {
     extern __shared__ __align__(16) unsigned char smem[];
     int64_t* sid = reinterpret_cast<int64_t*>(smem);                 // [mp2]
@@ -98,7 +82,7 @@ __global__ __launch_bounds__(256) void k_rerank(const float* __restrict__ Q, con
     for (int c = wv; c < m; c += 4) {
         const int row = crow[c];
         if (row < 0) continue;                    // uniform per wavefront
-        const T* p = corpus + (size_t)row * d;
+        const T* p = corpus + (size_t)row * ld;
         float acc = 0.0f;
         if (d4) {
             const V* p4 = reinterpret_cast<const V*>(p);

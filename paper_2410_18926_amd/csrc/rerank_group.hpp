@@ -90,6 +90,7 @@ struct GroupArgs {
     int64_t* out_ids;            // [nq][k]
     float* out_dists;            // [nq][k]
     int nq, d, m, k;
+    int ld;                      // elements from one stored row to the next
     int ht;                      // hash table slots (rerank_group_ht)
     int slices;                  // gather blocks per group
     int gq;                      // queries per group in this launch, <= G (the buffers keep their G-wide strides)
@@ -274,7 +275,7 @@ __global__ __launch_bounds__(kGatherThreads) void k_group_gather(GroupArgs a) {
 #pragma unroll
             for (int r = 0; r < RB; ++r) {
                 mk[r] = nmk[r]; ps[r] = nps[r];
-                const V* p4 = reinterpret_cast<const V*>(corpus + (size_t)nrow[r] * d);
+                const V* p4 = reinterpret_cast<const V*>(corpus + (size_t)nrow[r] * a.ld);
 #pragma unroll
                 for (int v = 0; v < NV; ++v) x[r][v] = row_load(p4 + min(lane + 64 * v, d4 - 1));
             }
@@ -309,7 +310,7 @@ __global__ __launch_bounds__(kGatherThreads) void k_group_gather(GroupArgs a) {
         for (int u = ubeg + wv; u < uend; u += kGatherWaves) {
             const int row = a.u_row[gbase + u];
             const uint32_t mk = a.u_mask[gbase + u];
-            const T* p = corpus + (size_t)row * d;
+            const T* p = corpus + (size_t)row * a.ld;
             for (int g = 0; g < ng; ++g) {
                 if (!((mk >> g) & 1u)) continue;
                 const float* qg = qs + (size_t)g * d;
@@ -469,7 +470,7 @@ __global__ __launch_bounds__(256) void k_small_rerank(GroupArgs a, int slices, i
 #pragma unroll
         for (int u = 0; u < 2; ++u) {                       // clamped: a repeat of the run's last candidate, not stored
             row[u] = a.cand[(size_t)q * m + min(t0 + 4 * u, t_end - 1)];
-            const V* p4 = reinterpret_cast<const V*>(corpus + (size_t)max(row[u], 0) * d);
+            const V* p4 = reinterpret_cast<const V*>(corpus + (size_t)max(row[u], 0) * a.ld);
 #pragma unroll
             for (int v = 0; v < NV; ++v) x[u][v] = row_load(p4 + min(lane + 64 * v, d4 - 1));
         }

@@ -1,0 +1,82 @@
+"""The screened re-rank (all candidates at half width, the few that can matter in full) against the kernel that evaluates every
+candidate of one query per block: bit-identical results (needs an MI355X)."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import oracle as O
+from tests.parity_util import assert_topk_equal, oracle_distance_of, rounding_abs_tol
+from tests.test_gpu_parity import _random_index
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def B():
+    from paper_2410_18926_amd import binding
+    assert torch.cuda.is_available(), "these tests need the GPU"
+    return binding
+
+
+# row lengths around the k-steps of 32, the register slices of 256 and their limits; candidate counts around the group sizes (16, 10,
+# 4, 1 queries), the wavefront and the block finish; k at the edge of the rule (4 k <= m); batches that end inside a group
+CASES = [(1, 0, 70, 100, 25), (3, 1, 65, 204, 10), (31, 2, 200, 205, 10), (32, 0, 129, 64, 16), (33, 1, 100, 300, 7), (255, 1, 90, 256, 64),
+         (256, 0, 333, 257, 10), (301, 2, 81, 777, 100), (516, 1, 66, 512, 128), (768, 0, 500, 200, 10), (768, 2, 30, 513, 1), (1023, 1, 70, 1024, 200),
+         (1024, 2, 111, 300, 10), (1028, 0, 66, 1025, 9), (1029, 1, 20, 1638, 11), (2000, 0, 70, 200, 10), (2050, 2, 67, 40, 10), (64, 1, 80, 4096, 1000),
+         (64, 0, 1, 600, 10), (96, 2, 9, 60, 15)]
+
+
+@pytest.mark.parametrize("half", [False, True])
+@pytest.mark.parametrize("d,metric,nq,m,k", CASES)
+def test_same_bits_as_the_plain_rerank(B, d, metric, nq, m, k, half):
+    rng = np.random.default_rng(31 * d + metric)
+    dp = 16 if d < 32 else 32
+    ix = _random_index(rng, n=7000, d=max(d, 16) if d < 16 else d, L=9, r=8, metric=metric, dp=dp)
+    d = ix["d"]
+    if metric != 2:       # heavy-tailed norms, elements in binary16's subnormal range, rows that are all zero
+        ix["corpus"] = (ix["corpus"] * np.exp(rng.normal(size=(7000, 1)) * 1.5)).astype(np.float32)
+        ix["corpus"][::53, ::3] *= np.float32(1e-6)
+        ix["corpus"][::701] = 0
+    ix["corpus"][1::2] = ix["corpus"][0::2] * np.float32(1 + 2.0 ** -9 if metric == 0 else 1)      # near-ties and ties
+    q = rng.normal(size=(nq, d)).astype(np.float32)
+    q[::7] *= np.float32(1e-4)
+    q[nq // 2] = 0
+    if nq > 3:
+        q[3] = ix["corpus"][4242]
+    gix = B.Index(**ix)
+    if half:
+        gix.set_rerank(B.RERANK_F16)
+    s_ids, s_d = gix.search(q, k, 6, m)
+    gix.set_exact_selection(True)
+    e_ids, e_d = gix.search(q, k, 6, m)
+    gix.set_exact_selection(False)
+    np.testing.assert_array_equal(s_ids, e_ids)
+    np.testing.assert_array_equal(s_d, e_d)
+    a = O.with_half_precision_corpus(ix) if half else ix
+    o_ids, o_d = O.search(O.OracleIndex(a), q, k, 6, m)
+    rows = a.get("rerank_corpus", ix["corpus"])
+    assert_topk_equal(s_ids, s_d, o_ids, o_d, f"d={d} metric={metric}", abs_tol=rounding_abs_tol(q, rows, metric) + (1e-6 if metric == 2 else 0.0),
+                      exact=oracle_distance_of(ix, q, rows))
+    gix.close()
+
+
+def test_queries_that_are_no_numbers_keep_every_candidate(B):
+    """An infinite or NaN query gives bounds that are no numbers: nothing may be dropped for the other queries of its group, and the call ends."""
+    rng = np.random.default_rng(5)
+    ix = _random_index(rng, n=3000, d=64, L=6, r=8, metric=0, dp=32)
+    q = rng.normal(size=(70, 64)).astype(np.float32)
+    clean = q.copy()
+    q[11, 3], q[40, 9] = np.nan, np.inf
+    q[50] *= np.float32(1e30)
+    q[51] *= np.float32(1e-30)
+    gix = B.Index(**ix)
+    ids, dist = gix.search(q, 5, 3, 100)
+    ref_ids, ref_d = gix.search(clean, 5, 3, 100)
+    good = np.setdiff1d(np.arange(70), [11, 40, 50, 51])
+    np.testing.assert_array_equal(ids[good], ref_ids[good])
+    np.testing.assert_array_equal(dist[good], ref_d[good])
+    gix.set_exact_selection(True)
+    e_ids, e_d = gix.search(q[50:52], 5, 3, 100)
+    np.testing.assert_array_equal(ids[50:52], e_ids)
+    np.testing.assert_array_equal(dist[50:52], e_d)
+    gix.close()
