@@ -503,10 +503,15 @@ int launch_screened_rerank(lorann_index* ix, Workspace& ws, hipStream_t s, const
     {
         Prof p(ix, K_TOPK, s);
         const int nv = d <= 1024 ? (d + 255) / 256 : 0;
-#define LAUNCH_SF5(L2_, NV_, V_, T_, NW_, EPL_) hipLaunchKernelGGL((k_screen_finish<L2_, NV_, V_, T_, NW_, EPL_>), dim3((unsigned)((nq * NW_ + 3) / 4)), dim3(256), (size_t)(4 / NW_) * 64 * NW_ * EPL_ * 12, s, ra)
-#define LAUNCH_SF4(L2_, NV_, T_, NW_, EPL_) do { if (d % 4 == 0 || NV_ == 0) LAUNCH_SF5(L2_, NV_, true, T_, NW_, EPL_); else LAUNCH_SF5(L2_, NV_, (NV_ == 0), T_, NW_, EPL_); } while (0)
-#define LAUNCH_SF3(L2_, NV_, T_) do { if (m <= 256) LAUNCH_SF4(L2_, NV_, T_, 1, 4); else if (m <= 512) LAUNCH_SF4(L2_, NV_, T_, 1, 8); \
-                                      else if (m <= 1024) LAUNCH_SF4(L2_, NV_, T_, 4, 4); else LAUNCH_SF4(L2_, 0, T_, 4, 16); } while (0)
+        // Up to two wavefronts per SIMD when a query has one: latency counts, four wavefronts share the query's rows (1000 queries,
+        // 128-d: 13.4 -> 11.4 us).  Beyond, the rows of other queries fill the memory pipe and the blocks only cost (10 000 queries,
+        // 768-d: 79 us with one wavefront, 87 with four; 1024-d: 118 and 165).
+        const bool wide = nq <= 2048;
+#define LAUNCH_SF5(L2_, NV_, V_, T_, SW_, RW_, EPL_) hipLaunchKernelGGL((k_screen_finish<L2_, NV_, V_, T_, SW_, RW_, EPL_>), dim3((unsigned)((nq * RW_ + 3) / 4)), dim3(256), (size_t)(4 / RW_) * 64 * SW_ * EPL_ * 12, s, ra)
+#define LAUNCH_SF4(L2_, NV_, T_, SW_, RW_, EPL_) do { if (d % 4 == 0 || NV_ == 0) LAUNCH_SF5(L2_, NV_, true, T_, SW_, RW_, EPL_); else LAUNCH_SF5(L2_, NV_, (NV_ == 0), T_, SW_, RW_, EPL_); } while (0)
+#define LAUNCH_SF3(L2_, NV_, T_) do { if (m <= 256) { if (wide) LAUNCH_SF4(L2_, NV_, T_, 1, 4, 4); else LAUNCH_SF4(L2_, NV_, T_, 1, 1, 4); } \
+                                      else if (m <= 512) { if (wide) LAUNCH_SF4(L2_, NV_, T_, 1, 4, 8); else LAUNCH_SF4(L2_, NV_, T_, 1, 1, 8); } \
+                                      else if (m <= 1024) LAUNCH_SF4(L2_, NV_, T_, 4, 4, 4); else LAUNCH_SF4(L2_, 0, T_, 4, 4, 16); } while (0)
 #define LAUNCH_SF2(L2_, NV_) do { if (half_rows) LAUNCH_SF3(L2_, NV_, _Float16); else LAUNCH_SF3(L2_, NV_, float); } while (0)
 #define LAUNCH_SF(L2_)                                                                                         \
     do {                                                                                                       \

@@ -388,46 +388,32 @@ __global__ __launch_bounds__(256) void k_screen_gather(ScreenRerankArgs a) {
     }
 }
 
-// NW wavefronts per query (1: four queries per block, 4: one); EPL candidates per lane, m <= 64 * NW * EPL.
-// grid = ceil(nq / (4 / NW)), block = 256, dynamic LDS = (4 / NW) * 64 * NW * EPL * 12 bytes.
+// SW wavefronts per query choose the survivors (EPL candidates per lane, m <= 64 * SW * EPL), RW of them read their rows:
+//   SW = RW = 1   four queries per block
+//   SW = 1, RW = 4   one query per block: the survivors' rows - about k - are in flight together
+//   SW = RW = 4   one query per block, many candidates
+// grid = ceil(nq / (4 / RW)), block = 256, dynamic LDS = (4 / RW) * 64 * SW * EPL * 12 bytes.
 // NV, T as in k_group_gather (NV = 0: any d); VEC: d % 4 == 0, a lane owns elements 4 (lane + 64 v) .. + 3, else elements lane + 64 j.
-// About k + a few rows per query are read in full, the candidates' approximate values are all in registers.
-template <bool L2, int NV, bool VEC, typename T, int NW, int EPL>
+template <bool L2, int NV, bool VEC, typename T, int SW, int RW, int EPL>
 __global__ __launch_bounds__(256) void k_screen_finish(ScreenRerankArgs a) {
     const bool cosine = a.metric == 2;
-    constexpr int QPB = 4 / NW, CAP = 64 * NW * EPL;
-    constexpr int RB = NV == 0 ? 1 : sizeof(T) == 2 || NV <= 2 ? 4 : 2;     // rows in flight per wavefront
+    constexpr int QPB = 4 / RW, CAP = 64 * SW * EPL;
+    constexpr int RB = NV == 0 ? 1 : RW == 4 || sizeof(T) == 2 || NV <= 2 ? 4 : 2;     // rows in flight per wavefront
     using V = typename Row4<T>::type;
     extern __shared__ __align__(16) unsigned char smem[];
     __shared__ int s_cnt[4], s_part[2][4];
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-    const int sub = NW == 1 ? wv : 0, w0 = NW == 1 ? 0 : wv;             // query of the block, wavefront of the query
+    const int sub = RW == 1 ? wv : 0, w0 = RW == 1 ? 0 : wv;             // query of the block, wavefront of the query
     const int64_t q = (int64_t)blockIdx.x * QPB + sub;
-    if (q >= a.nq) return;                                               // NW = 4: never; NW = 1: wavefronts are independent
+    if (q >= a.nq) return;                                               // RW = 4: never; RW = 1: wavefronts are independent
     int64_t* s_id = reinterpret_cast<int64_t*>(smem) + (size_t)sub * CAP;                                   // row, then id of each survivor
     uint32_t* s_key = reinterpret_cast<uint32_t*>(smem + (size_t)QPB * CAP * 8) + (size_t)sub * CAP;        // order-preserving key of its distance
-    auto meet = [&]() { if (NW == 1) wave_lds_sync(); else __syncthreads(); };
+    auto meet = [&]() { if (RW == 1) wave_lds_sync(); else __syncthreads(); };
+    auto meet_sel = [&]() { if (SW == 1) wave_lds_sync(); else __syncthreads(); };
     const int m = a.m, d = a.d;
     const int32_t* crow = a.cand + (size_t)q * m;
     const uint16_t* erow = a.entry + (size_t)q * m;
     const size_t gbase = (size_t)a.qgroup[q] * a.gstride;
-    int row[EPL], at[EPL];
-    float lo[EPL];
-    uint32_t key[EPL];
-#pragma unroll
-    for (int e = 0; e < EPL; ++e) {                                       // clamped addresses: the loads go out together
-        const int t = (e * NW + w0) * 64 + lane, tc = min(t, m - 1);
-        row[e] = crow[tc];
-        at[e] = erow[tc];
-        if (t >= m) row[e] = -1;
-    }
-#pragma unroll
-    for (int e = 0; e < EPL; ++e) {
-        const size_t ec = gbase + (row[e] >= 0 ? at[e] : 0);
-        if (L2) { const float2 b = reinterpret_cast<const float2*>(a.approx)[ec]; lo[e] = b.x; key[e] = float_key_asc(b.y); }
-        else { lo[e] = a.approx[ec]; key[e] = float_key_asc(lo[e]); }
-    }
-    const float4 qs = a.qstat[q];
     const int ldr = sizeof(T) == 2 ? a.ld : d;
     const T* corpus = static_cast<const T*>(a.corpus);
     const float* qrow = a.Q + (size_t)q * d;
@@ -444,12 +430,30 @@ __global__ __launch_bounds__(256) void k_screen_finish(ScreenRerankArgs a) {
         for (int i = lane; i < d; i += 64) acc = fmaf(qrow[i], qrow[i], acc);
         qn = sqrtf(wave_sum_f32(acc));
     }
+    if (SW == RW || w0 == 0) {                                            // uniform over the wavefront
+    const float4 qs = a.qstat[q];
+    int row[EPL], at[EPL];
+    float lo[EPL];
+    uint32_t key[EPL];
+#pragma unroll
+    for (int e = 0; e < EPL; ++e) {                                       // clamped addresses: the loads go out together
+        const int t = (e * SW + w0) * 64 + lane, tc = min(t, m - 1);
+        row[e] = crow[tc];
+        at[e] = erow[tc];
+        if (t >= m) row[e] = -1;
+    }
+#pragma unroll
+    for (int e = 0; e < EPL; ++e) {
+        const size_t ec = gbase + (row[e] >= 0 ? at[e] : 0);
+        if (L2) { const float2 b = reinterpret_cast<const float2*>(a.approx)[ec]; lo[e] = b.x; key[e] = float_key_asc(b.y); }
+        else { lo[e] = a.approx[ec]; key[e] = float_key_asc(lo[e]); }
+    }
     int par = 0;
     auto count = [&](auto f) {                                            // over all candidates of the query (uniform result)
         int c = 0;
 #pragma unroll
         for (int e = 0; e < EPL; ++e) c += __popcll(__ballot(row[e] >= 0 && f(e)));
-        if (NW > 1) {
+        if (SW > 1) {
             if (lane == 0) s_part[par][wv] = c;
             __syncthreads();
             c = s_part[par][0] + s_part[par][1] + s_part[par][2] + s_part[par][3];
@@ -472,7 +476,7 @@ __global__ __launch_bounds__(256) void k_screen_finish(ScreenRerankArgs a) {
     thr += 1e-6f * fabsf(thr);
     if (cosine && !(qn > 1e-15f)) thr = NAN;          // (a zero query ties with everything: nothing is dropped)
     if (lane == 0 && w0 == 0) s_cnt[sub] = 0;
-    meet();
+    meet_sel();
 #pragma unroll
     for (int e = 0; e < EPL; ++e) {
         const bool in = row[e] >= 0 && !(lo[e] > thr);
@@ -481,6 +485,7 @@ __global__ __launch_bounds__(256) void k_screen_finish(ScreenRerankArgs a) {
         if (lane == 0 && mk) base = atomicAdd(&s_cnt[sub], __popcll(mk));
         base = __builtin_amdgcn_readfirstlane(base);
         if (in) s_id[base + __popcll(mk & ((1ull << lane) - 1ull))] = row[e];
+    }
     }
     meet();
     const int c = s_cnt[sub];
@@ -491,7 +496,7 @@ __global__ __launch_bounds__(256) void k_screen_finish(ScreenRerankArgs a) {
         else dist = qn > 0.0f ? 1.0f - acc / qn : 1.0f;
         s_key[i] = min(float_key_asc(dist), float_key_asc(INFINITY));
     };
-    for (int i0 = w0 * RB; i0 < c; i0 += NW * RB) {
+    for (int i0 = w0 * RB; i0 < c; i0 += RW * RB) {
         if constexpr (NV > 0) {
             float4 x[RB][NV];
             if constexpr (VEC) {
@@ -573,7 +578,7 @@ __global__ __launch_bounds__(256) void k_screen_finish(ScreenRerankArgs a) {
     }
     meet();
     // rows -> ids, each by the thread that ranks the survivor
-    const int first = w0 * 64 + lane, step = 64 * NW;
+    const int first = w0 * 64 + lane, step = 64 * RW;
     for (int i = first; i < c; i += step) { const int64_t rw = s_id[i]; s_id[i] = a.ids ? a.ids[rw] : rw; }
     meet();
     for (int i = first; i < c; i += step) {
