@@ -24,6 +24,7 @@
 #include "screen.hpp"
 #include "select_exact.hpp"
 #include "select_query.hpp"
+#include "select_wave.hpp"
 #include "small_batch.hpp"
 #include "screen_fused.hpp"
 #include "stage_a.hpp"
@@ -103,6 +104,7 @@ struct Workspace {
     DevBuf qproj, qbf, q8, dx, gscore, sel, count, rank_in_bucket, qrank, qorder, qorder2, off0, base_tab, bucket_off, tile_off, unit_off, slot_of_pos, pos_of_slot, Z, sigma, rho0, cand;
     DevBuf tau, n_kept, fb_list, pmax, voff, qkey, u_row, u_mask, u_pos, u_count, rdist, rcid, rccount;
     DevBuf smin, thr, hit_val, hit_grp, hit_cnt;      // screening without the matrix of approximate values
+    DevBuf submax;                                    // quarter maxima of large clusters
     DevBuf qhalf, qstat, u_meta;                      // screened re-rank (its other lists share u_row, u_pos, u_count, rdist and rccount)
     hipStream_t stream = nullptr;          // lanes >= 1: created on first use, default priority
     hipEvent_t fork = nullptr, join = nullptr;
@@ -113,7 +115,7 @@ struct Workspace {
         if (arena) return;
         DevBuf* bufs[] = {&qproj, &qbf, &q8, &dx, &gscore, &sel, &count, &rank_in_bucket, &qrank, &qorder, &qorder2, &off0, &base_tab, &bucket_off, &tile_off,
                           &unit_off, &slot_of_pos, &pos_of_slot, &Z, &sigma, &rho0, &cand, &tau, &n_kept, &fb_list, &pmax, &voff, &qkey, &u_row, &u_mask, &u_pos, &u_count, &rdist, &rcid, &rccount,
-                          &smin, &thr, &hit_val, &hit_grp, &hit_cnt, &qhalf, &qstat, &u_meta};
+                          &smin, &thr, &hit_val, &hit_grp, &hit_cnt, &submax, &qhalf, &qstat, &u_meta};
         for (DevBuf* b : bufs) b->release();
         if (fork) (void)hipEventDestroy(fork);
         if (gather_done) (void)hipEventDestroy(gather_done);
@@ -154,6 +156,7 @@ int scratch_of_device(int dev, void** out) {
 struct lorann_index {
     int32_t metric = 0, d = 0, dp = 0, r = 0, r_pad = 0, L = 0;
     int64_t n = 0;
+    int64_t max_cluster = 0;        // points of the largest cluster
     hipStream_t stream = nullptr;
     // index data (device)
     float* centroids = nullptr;     // [L][dp]
@@ -307,6 +310,7 @@ int prof_settle(lorann_index* ix) {
 
 int next_pow2(int v) { int p = 1; while (p < v) p <<= 1; return p; }
 
+constexpr int kSubMaxItems = 192 * 1024; // quarter maxima of at most this many scoring work items are kept (1 KiB each)
 constexpr int kSmallPathQueries = 64;   // batches up to this size take the query-major path
 constexpr int kNZ = 2;                 // 32-pair tiles per scoring unit
 constexpr int kUnitPairs = 32 * kNZ;
@@ -319,7 +323,7 @@ inline bool pair_max_streams(int64_t npairs, int L) { return npairs <= (int64_t)
 
 // S7 on the int8 matrix cores: the best score of every (query, cluster) pair.  With y_off / y (verification) the
 // instantiation that also stores every accumulator is launched instead.
-void launch_pair_max(lorann_index* ix, Workspace& ws, hipStream_t s, int64_t npairs, const int64_t* y_off, int32_t* y, bool small = false) {
+void launch_pair_max(lorann_index* ix, Workspace& ws, hipStream_t s, int64_t npairs, const int64_t* y_off, int32_t* y, bool small = false, int sub_cap = 0) {
     const int L = small ? (int)npairs : ix->L;       // small batches: every pair is a cluster of its own
     const bool l2 = ix->metric == LORANN_L2, mixed = ix->A_first != nullptr;
     const int ks = ix->r_pad / 32;
@@ -329,6 +333,7 @@ void launch_pair_max(lorann_index* ix, Workspace& ws, hipStream_t s, int64_t npa
     sc.sqnorm = l2 ? ix->sqnorm : nullptr; sc.pt_scale = ix->sB_pts; sc.pt_first = ix->B_first; sc.rho0 = mixed ? ws.rho0.as<float>() : nullptr; sc.pmax = ws.pmax.as<uint32_t>(); sc.L = L; sc.chunk_tiles = kChunkTiles;
     sc.slot_of_pos = ws.slot_of_pos.as<int32_t>(); sc.y_off = y_off; sc.y = y;
     sc.voff = small ? ws.voff.as<int64_t>() : nullptr;
+    sc.sub = sub_cap > 0 ? ws.submax.as<uint32_t>() : nullptr; sc.sub_cap = sub_cap;
     // few pairs per cluster: the kernel streams the codes of the touched clusters, one wavefront per cluster
     const bool stream = small || pair_max_streams(npairs, L);
     const dim3 gs((unsigned)((L + 3) / 4)), gp(2048);   // persistent shape: 8192 wavefronts stride over the work items
@@ -356,6 +361,8 @@ struct ChunkPlan {
     bool mixed, screen, fused_quant, big_matrix, lds_hist, grouped;
     bool handful;       // up to 8 queries: distances and top-k of the re-rank in one launch
     bool screened;      // re-rank screened by the binary16 copy of the corpus
+    bool wave_walk;     // candidate selection by one wavefront per query
+    int sub_cap;        // scoring work items whose quarter maxima are kept (large clusters; 0: none)
     int screen_gq;      // queries per group of the screened re-rank
     int screen_stride;  // list entries per group
     bool small;         // query-major path of small batches (no bucketing)
@@ -365,7 +372,7 @@ struct ChunkPlan {
     int64_t ngroups;
 };
 
-ChunkPlan plan_chunk(const lorann_index* ix, int64_t nq, int k, int w, int m, bool allow_screened = true) {
+ChunkPlan plan_chunk(const lorann_index* ix, int64_t nq, int k, int w, int m, bool fixed = false, bool allow_screened = true) {
     ChunkPlan pl;
     const int L = ix->L;
     pl.mixed = ix->A_first != nullptr;      // Sec. 4.2: first component of q' and of every r stay in float
@@ -391,6 +398,17 @@ ChunkPlan plan_chunk(const lorann_index* ix, int64_t nq, int k, int w, int m, bo
     // A few dozen queries: hardly two pairs share a cluster, so the pairs stay in slot order and every launch that only
     // serves the bucketing is left out (per-cluster step sizes only).
     pl.small = nq <= kSmallPathQueries && pl.screen && !pl.mixed && ix->sA_cols == nullptr && ix->rerank_mode != LORANN_RERANK_NONE;
+    // Candidate selection: one wavefront per query where many queries share the machine and its short list suffices (microseconds,
+    // four wavefronts per query / one: 10 000 queries of the 768-d workload 104 / 74, 2531 queries with m = 777 209 / 140, 10M points
+    // 960 / 498 per 100 000 queries; 1000 queries 15 / 19, 1024 queries at 10M points 23 / 27).  A large
+    // cluster would keep such a wavefront busy on its own, so its quarter maxima have to be there (work items only, and not in the
+    // fixed region, which they would fill), else four wavefronts share it.
+    const bool items = nq > 2048 && !pair_max_streams(nq * w, L);
+    const int64_t max_items = ((int64_t)nq * w / kUnitPairs + L) * (((ix->max_cluster - 1) >> kChunkShift) + 1);     // at most
+    pl.sub_cap = items && !fixed && ix->max_cluster > kSubMinPoints ? (int)std::min<int64_t>(max_items, kSubMaxItems) : 0;
+    pl.wave_walk = nq > 2048 && !ix->force_exact && m <= kSelectWaveMaxM && select_wave_lds(select_wave_epl(m), w) <= 64 * 1024 && ix->max_cluster <= kSelectWaveMaxCluster &&
+                   (ix->max_cluster <= 4 * kSubMinPoints || pl.sub_cap > 0);
+    if (!pl.wave_walk) pl.sub_cap = 0;
     pl.handful = pl.small && pl.grouped && nq <= 8 && ix->d % 4 == 0 && ix->d <= 1024 && k <= 64;
     // The screened re-rank reads all candidates at half width and about k of them in full: it pays while k is a small part of m
     // (a row read at half width is shared by about two queries, one read in full is not, so up to k = m / 4).  A few dozen queries are
@@ -435,6 +453,7 @@ int reserve_workspace(const lorann_index* ix, Workspace& ws, const ChunkPlan& pl
         {&ws.rdist, sgroups * (ix->metric == LORANN_L2 ? 8 : 4), pl.screened},
         {&ws.rdist, q * m * 4, pl.grouped || no_rerank}, {&ws.rcid, q * m * 8, pl.grouped || no_rerank},
         {&ws.rccount, q * 4, pl.grouped || no_rerank || pl.small},      // (small batches: also the tickets of the one-launch re-rank)
+        {&ws.submax, (size_t)pl.sub_cap * kUnitPairs * 16, pl.sub_cap > 0},
         {&ws.smin, q * kFusedSubsets * 4, pl.digest}, {&ws.thr, q * 4, pl.digest},
         {&ws.hit_val, q * kFusedLists * kFusedCap * 64, pl.digest}, {&ws.hit_grp, q * kFusedLists * kFusedCap * 4, pl.digest},
         {&ws.hit_cnt, q * kFusedLists * 4, pl.digest},
@@ -455,10 +474,10 @@ int reserve_workspace(const lorann_index* ix, Workspace& ws, const ChunkPlan& pl
 
 // The plan of a batch and its buffers.  A search that fits the fixed region only without the screened re-rank's lists goes without.
 int plan_and_reserve(const lorann_index* ix, Workspace& ws, int64_t nq, int k, int w, int m, ChunkPlan& pl) {
-    pl = plan_chunk(ix, nq, k, w, m);
+    pl = plan_chunk(ix, nq, k, w, m, ws.arena != nullptr);
     int rc = reserve_workspace(ix, ws, pl, nq, w, m);
     if (rc == LORANN_E_UNSUPPORTED && ws.arena && pl.screened) {
-        pl = plan_chunk(ix, nq, k, w, m, false);
+        pl = plan_chunk(ix, nq, k, w, m, true, false);
         rc = reserve_workspace(ix, ws, pl, nq, w, m);
     }
     return rc;
@@ -732,7 +751,7 @@ int search_chunk(lorann_index* ix, Workspace& ws, hipStream_t s, const float* dQ
         const int ks = r_pad / 32;
         {
             Prof p(ix, K_PAIR_MAX, s);
-            launch_pair_max(ix, ws, s, npairs, nullptr, nullptr, pl.small);
+            launch_pair_max(ix, ws, s, npairs, nullptr, nullptr, pl.small, pl.sub_cap);
         }
         {
             Prof p(ix, K_SELECT_QUERY, s);
@@ -741,23 +760,34 @@ int search_chunk(lorann_index* ix, Workspace& ws, hipStream_t s, const float* dQ
             qa.Z = ws.Z.as<int8_t>(); qa.sigma = ws.sigma.as<float>(); qa.Bp = ix->Bp; qa.off = ix->off; qa.sqnorm = l2 ? ix->sqnorm : nullptr; qa.pt_scale = ix->sB_pts; qa.pt_first = ix->B_first; qa.rho0 = mixed ? ws.rho0.as<float>() : nullptr;
             qa.cand = ws.cand.as<int32_t>(); qa.tau = ws.tau.as<float>(); qa.n_kept = ws.n_kept.as<int32_t>(); qa.qkey = ws.qkey.as<int32_t>();
             qa.fb_list = ws.fb_list.as<int32_t>(); qa.fb_count = ws.count.as<int32_t>() + 2 * L; qa.qorder = ws.qorder.as<int32_t>(); qa.nq = (int)nq; qa.w = w; qa.m = m; qa.cap = select_query_cap(m);
-            const size_t qlds = (size_t)qa.cap * 8;
+            const size_t qlds = select_query_lds(qa.cap, w);
             qa.run_shift = 6;
             const int64_t round = (int64_t)8 << qa.run_shift;
             const dim3 qgrid((unsigned)(round * ((nq + round - 1) / round)));
-            if (pl.small && qa.cap == 2048) {
-                if (ks == 1) hipLaunchKernelGGL((k_select_query<2, 2, true>), qgrid, dim3(256), qlds, s, qa);
-                else hipLaunchKernelGGL((k_select_query<4, 2, true>), qgrid, dim3(256), qlds, s, qa);
-            } else if (pl.small) {
-                if (ks == 1) hipLaunchKernelGGL((k_select_query<2, 6, true>), qgrid, dim3(256), qlds, s, qa);
-                else hipLaunchKernelGGL((k_select_query<4, 6, true>), qgrid, dim3(256), qlds, s, qa);
-            } else if (qa.cap == 2048) {
-                if (ks == 1) hipLaunchKernelGGL((k_select_query<2, 2>), qgrid, dim3(256), qlds, s, qa);
-                else hipLaunchKernelGGL((k_select_query<4, 2>), qgrid, dim3(256), qlds, s, qa);
-            } else {
-                if (ks == 1) hipLaunchKernelGGL((k_select_query<2, 6>), qgrid, dim3(256), qlds, s, qa);
-                else hipLaunchKernelGGL((k_select_query<4, 6>), qgrid, dim3(256), qlds, s, qa);
-            }
+            const bool ext = ix->sB_pts != nullptr;
+#define LAUNCH_SQ3(RB_, L2_, EXT_) do { if (pl.small) hipLaunchKernelGGL((k_select_query<RB_, L2_, EXT_, true>), qgrid, dim3(256), qlds, s, qa); \
+                                        else hipLaunchKernelGGL((k_select_query<RB_, L2_, EXT_, false>), qgrid, dim3(256), qlds, s, qa); } while (0)
+#define LAUNCH_SQ2(RB_, L2_) do { if (ext) LAUNCH_SQ3(RB_, L2_, true); else LAUNCH_SQ3(RB_, L2_, false); } while (0)
+#define LAUNCH_SQ(RB_) do { if (l2) LAUNCH_SQ2(RB_, true); else LAUNCH_SQ2(RB_, false); } while (0)
+            qa.sub = pl.sub_cap > 0 ? ws.submax.as<uint32_t>() : nullptr; qa.bucket_off = ws.bucket_off.as<int32_t>(); qa.unit_off = ws.unit_off.as<int32_t>(); qa.sub_cap = pl.sub_cap;
+            if (pl.wave_walk) {
+                const int epl = select_wave_epl(m);
+                const size_t wlds = select_wave_lds(epl, w);
+                const int64_t wround = (int64_t)32 << (qa.run_shift - 2);          // queries per eight runs of blocks
+                const dim3 wgrid((unsigned)(wround / 4 * ((nq + wround - 1) / wround)));
+#define LAUNCH_SW4(RB_, L2_, EXT_) do { if (epl == 8) hipLaunchKernelGGL((k_select_wave<RB_, L2_, EXT_, 8>), wgrid, dim3(256), wlds, s, qa); \
+                                        else hipLaunchKernelGGL((k_select_wave<RB_, L2_, EXT_, 16>), wgrid, dim3(256), wlds, s, qa); } while (0)
+#define LAUNCH_SW2(RB_, L2_) do { if (ext) LAUNCH_SW4(RB_, L2_, true); else LAUNCH_SW4(RB_, L2_, false); } while (0)
+#define LAUNCH_SW(RB_) do { if (l2) LAUNCH_SW2(RB_, true); else LAUNCH_SW2(RB_, false); } while (0)
+                if (ks == 1) LAUNCH_SW(2); else LAUNCH_SW(4);
+#undef LAUNCH_SW
+#undef LAUNCH_SW2
+#undef LAUNCH_SW4
+            } else if (ks == 1) LAUNCH_SQ(2);
+            else LAUNCH_SQ(4);
+#undef LAUNCH_SQ
+#undef LAUNCH_SQ2
+#undef LAUNCH_SQ3
         }
         sa_.qlist = ws.fb_list.as<int32_t>(); sa_.qcount = ws.count.as<int32_t>() + 2 * L;
         sa_.fb_total = fb_total;      // asynchronous searches being profiled: the count is added up on the device
@@ -1155,6 +1185,7 @@ int lorann_load_index(lorann_index** out, int32_t metric, int64_t n, int32_t d, 
     }
     ix->metric = metric; ix->n = n; ix->d = d; ix->dp = dp; ix->r = r; ix->L = L;
     ix->r_pad = r <= 32 ? 32 : 64;
+    for (int c = 0; c < L; ++c) ix->max_cluster = std::max(ix->max_cluster, off[c + 1] - off[c]);
     int rc = LORANN_OK;
     auto body = [&]() -> int {
         int e;

@@ -35,12 +35,19 @@ struct ScoreArgs {
                                  // is then simply pair c (bucket_off is not read: pairs [c, c + 1)); else NULL
     int L;
     int chunk_tiles;             // 32-point tiles per work item
+    // clusters of more than kSubMinPoints points (items only): also the best score of every quarter of an item's points - those
+    // whose place in their 32-point tile is 8 s .. 8 s + 7 - as keys, [items][pairs of an item][4], so that the candidate selection
+    // can dismiss most of a large cluster; items from sub_cap on have none
+    uint32_t* sub;
+    int sub_cap;
     // verification only (DUMP instantiations): every int32 accumulator of the matrix-core product is written to
     // y[y_off[slot_of_pos[pair]] + point]
     const int32_t* slot_of_pos;  // [npairs] bucket position -> slot (query * w + rank)
     const int64_t* y_off;        // [npairs + 1] offsets of the slots into y
     int32_t* y;
 };
+
+constexpr int kSubMinPoints = 2048;
 
 // Row (within the 32-row tile) of result register v for lane half h.
 __device__ __forceinline__ int tile_row(int v, int h) { return 8 * (v >> 2) + 4 * h + (v & 3); }
@@ -83,7 +90,7 @@ __global__ __launch_bounds__(64 * WPB) void k_pair_max(ScoreArgs a) {
     // no block-wide barrier below: the wavefronts of a block are independent
 
     // pairs [pb, min(pb + NP, pend)) against rows [row0, row0 + m_c); row0 is point pt0 of its cluster
-    auto process = [&](int pb, int pend, int64_t row0, int m_c, int pt0) {
+    auto process = [&](int pb, int pend, int64_t row0, int m_c, int pt0, uint32_t* sub) {
         i32x4 zreg[NZ][KS];
 #pragma unroll
         for (int z = 0; z < NZ; ++z) {
@@ -237,17 +244,31 @@ __global__ __launch_bounds__(64 * WPB) void k_pair_max(ScoreArgs a) {
             const int z = p >> 5, i = p & 31;
             const int hh = (i >> 2) & 1, v = 4 * (i >> 3) + (i & 3);        // inverse of tile_row
             const int* col = &s_tr[wv][hh * 32 * TRS + z * 16 + v];
+            uint32_t quarter[4];
             if (!FLT) {
                 int r = IMIN;
 #pragma unroll
-                for (int jj = 0; jj < 32; ++jj) r = max(r, col[jj * TRS]);
+                for (int s = 0; s < 4; ++s) {
+                    int rs = IMIN;
+#pragma unroll
+                    for (int jj = 8 * s; jj < 8 * s + 8; ++jj) rs = max(rs, col[jj * TRS]);
+                    r = max(r, rs);
+                    if (sub) quarter[s] = rs != IMIN && pb + p < pend ? float_key_asc(__fmaf_rn((float)rs, a.sigma[pb + p], -0.0f)) : 0u;
+                }
                 s_red[wv][p] = r;
             } else {
                 unsigned r = 0u;
 #pragma unroll
-                for (int jj = 0; jj < 32; ++jj) r = max(r, (unsigned)col[jj * TRS]);
+                for (int s = 0; s < 4; ++s) {
+                    unsigned rs = 0u;
+#pragma unroll
+                    for (int jj = 8 * s; jj < 8 * s + 8; ++jj) rs = max(rs, (unsigned)col[jj * TRS]);
+                    r = max(r, rs);
+                    quarter[s] = rs == float_key_asc(-INFINITY) ? 0u : rs;
+                }
                 s_red[wv][p] = (int)r;
             }
+            if (sub) *reinterpret_cast<uint4*>(sub + 4 * p) = make_uint4(quarter[0], quarter[1], quarter[2], quarter[3]);      // (uniform)
         }
         wave_lds_sync();
         for (int p = lane; p < NP; p += 64) {
@@ -274,7 +295,7 @@ __global__ __launch_bounds__(64 * WPB) void k_pair_max(ScoreArgs a) {
             if (pbeg == pend) continue;
             const int64_t row_c = a.voff ? a.voff[2 * c] : a.off[c];
             const int m_all = (int)((a.voff ? a.voff[2 * c + 1] : a.off[c + 1]) - row_c);
-            for (int pb = pbeg; pb < pend; pb += NP) process(pb, pend, row_c, m_all, 0);
+            for (int pb = pbeg; pb < pend; pb += NP) process(pb, pend, row_c, m_all, 0, nullptr);
         }
     } else {
         const int n_items = a.unit_off[a.L];
@@ -289,7 +310,8 @@ __global__ __launch_bounds__(64 * WPB) void k_pair_max(ScoreArgs a) {
             // so the chunk's codes are fetched from L2 once per block
             const int pk = local / n_groups, ug = local - pk * n_groups;
             process(pbeg + ug * NP, pend, row_c + (int64_t)pk * 32 * a.chunk_tiles,
-                    min(32 * a.chunk_tiles, m_all - pk * 32 * a.chunk_tiles), pk * 32 * a.chunk_tiles);
+                    min(32 * a.chunk_tiles, m_all - pk * 32 * a.chunk_tiles), pk * 32 * a.chunk_tiles,
+                    m_all > kSubMinPoints && item < a.sub_cap ? a.sub + (size_t)item * (4 * NP) : nullptr);
         }
     }
 }

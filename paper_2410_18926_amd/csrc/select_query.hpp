@@ -2,14 +2,14 @@
 // paper's candidate count t is called m here).
 //
 // k_pair_max has already computed, for every (query, cluster) pair, the best score of the cluster.  One block
-// per query now walks the query's pairs in descending order of that best score and keeps a running threshold T =
-// the m-th best score seen so far: a cluster whose best score is below T cannot contribute a candidate, and
+// per query now walks the query's pairs in descending order of that best score and keeps a running threshold T,
+// at most the m-th best score seen so far: a cluster whose best score is below T cannot contribute a candidate, and
 // because the pairs are sorted the walk stops at the first such cluster.  A query's best candidates sit in very
 // few of its w clusters, so typically one or two clusters are scored here (point-parallel, 4-way int8 dot
-// products); all the others were dismissed by their maxima alone.  The scores that reach T are held in LDS, the
-// threshold is tightened by an exact radix select whenever new ones arrive, and the final exact top-m (score
-// descending, row ascending) is written out.  Only if more scores tie with T than LDS can hold does the query go
-// to the exact per-query kernel.
+// products); all the others were dismissed by their maxima alone.  The scores that reach T are held in LDS and counted
+// in bins, off which T is read whenever new ones have arrived; the exact top-m (score descending, row ascending) is
+// selected once, at the end.  Only if more scores tie with T than LDS can hold does the query go to the exact
+// per-query kernel.
 #pragma once
 #include "common.hpp"
 #include "select_exact.hpp"
@@ -60,8 +60,7 @@ __device__ __forceinline__ uint32_t block_mth_largest(int n, int m, int* hist, u
 }
 
 
-// (score, row) entries a query holds in LDS: 2048 (16 KiB, more blocks per CU) or 6144 for m > 1024.  A quarter
-// of the capacity is scored between capacity checks.
+// (score, row) entries a query holds in LDS: 2048 (16 KiB, more blocks per CU) or 6144 for m > 1024.
 inline int select_query_cap(int m) { return m <= 1024 ? 2048 : 6144; }
 
 // Block-wide minimum of `v` written to *dst (scratch: one int of LDS, clobbered).  Contains barriers.
@@ -74,6 +73,18 @@ __device__ __forceinline__ void block_min_to(int32_t* dst, int v, int* scratch) 
     __syncthreads();
     if (threadIdx.x == 0) *dst = *scratch;
 }
+
+// Scores are counted in bins of their distance from the query's best one (known from the pair maxima), in the order-preserving
+// key space: distances below 64 have a bin each, beyond that 64 bins per power of two, so the m-th best score is known to
+// 1/64 of its distance from the best at any time, whatever the scores' scale.  (Sixteen per power of two left several hundred entries
+// in the last bin at m = 300 and above, and ranking those took longer than the walk's last clusters.)
+constexpr int kSelectBins = 1792;      // 28 * 64 >= 64 + 26 * 64
+__device__ __forceinline__ int select_bin(uint32_t dist) {
+    const int e = 31 - __clz((int)(dist | 1u));
+    return e < 6 ? (int)dist : (e - 5) * 64 + (int)((dist >> (e - 6)) & 63u);
+}
+__device__ __forceinline__ uint32_t select_bin_first(int bin) { return bin < 64 ? (uint32_t)bin : (uint32_t)(64 + (bin & 63)) << ((bin >> 6) - 1); }
+__device__ __forceinline__ uint32_t select_bin_last(int bin) { return select_bin_first(bin + 1) - 1u; }       // (wraps to 2^32 - 1 in the last bin)
 
 struct QuerySelectArgs {
     const int32_t* sel;          // [nq][w] clusters of each query
@@ -97,29 +108,47 @@ struct QuerySelectArgs {
     int nq, w, m;
     int cap;                     // select_query_cap(m)
     int run_shift;               // log2 of the queries per run (see the kernel)
+    // large clusters (score_mfma.hpp), one-wavefront kernel only: best scores of the quarters of every work item, or NULL
+    const uint32_t* sub;         // [items][64][4]
+    const int32_t* bucket_off;   // [L+1]
+    const int32_t* unit_off;     // [L+1]
+    int sub_cap;                 // items that have them
 };
 
-// grid = 512 * ceil(nq / 512), block = 256, dynamic LDS = 8 * cap bytes.  RB = r_pad / 16.
+// Dynamic LDS of k_select_query: the list and what is known of each pair.
+inline size_t select_query_lds(int cap, int w) { return (size_t)cap * 8 + (size_t)w * 28; }
+
+// grid = 512 * ceil(nq / 512), block = 256, dynamic LDS = select_query_lds bytes.  RB = r_pad / 16; EXT: column-wise step sizes
+// (and, if pt_first is given, the mixed-precision decomposition).
 // Queries are visited grouped by nearest cluster (workgroups are dealt round-robin over the 8 XCDs): queries that
 // score the same cluster run together and share its codes in L2.
-// PT = points a thread scores between two capacity checks = cap / 1024.
 // INLINE_FB (small batches): a query whose survivor list overflows is finished right here by the exact per-query
 // routine instead of being handed to a later launch.
-template <int RB, int PT, bool INLINE_FB = false>
+//
+// Bound by latency: a typical query scores one or two clusters of a thousand points.  So everything about the w pairs is fetched in
+// one round trip, the four wavefronts walk a cluster on their own - pieces of 64 PT points, two pieces requested ahead, scores that
+// reach T appended under one atomic per wavefront - and meet only at its end (or when the list is nearly full), where one wavefront
+// reads the new T off the bins.  The exact selection happens once, over the few entries of the m-th score's bin.
+template <int RB, bool L2, bool EXT, bool INLINE_FB>
 __global__ __launch_bounds__(256) void k_select_query(QuerySelectArgs a) {
-    constexpr int ZW = RB * 4;
+    constexpr int ZW = RB * 4, PT = RB == 2 ? 2 : 1, PIECE = 64 * PT;
     extern __shared__ __align__(16) unsigned char qs_smem[];
-    uint32_t* keys = reinterpret_cast<uint32_t*>(qs_smem);
-    int32_t* rows = reinterpret_cast<int32_t*>(qs_smem + (size_t)a.cap * 4);
-    const int kQCap = a.cap, kQChunk = a.cap >> 2;
-    __shared__ int zw[ZW];
+    const int tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int w = a.w, m = a.m, cap = a.cap;
+    uint32_t* keys = reinterpret_cast<uint32_t*>(qs_smem);               // [cap]
+    int32_t* rows = reinterpret_cast<int32_t*>(keys + cap);              // [cap]
+    uint32_t* pk = reinterpret_cast<uint32_t*>(rows + cap);              // [w] key of the pair's best score
+    int* ppos = reinterpret_cast<int*>(pk + w);                          // [w] position of the pair, first row, points, scale, first component of r
+    int* prow = ppos + w;
+    int* pcnt = prow + w;
+    float* psig = reinterpret_cast<float*>(pcnt + w);
+    float* prho = psig + w;
+    int* order = reinterpret_cast<int*>(prho + w);
+    __shared__ __align__(16) int bins[kSelectBins];                                    // later: (key, row) entries of one bin
     __shared__ int hist[256];
     __shared__ int wsum[4];
-    __shared__ uint32_t sh[2];
-    __shared__ uint32_t pk[256];      // best-score keys of the query's pairs
-    __shared__ int ppos[256], order[256];
-    __shared__ int s_count, s_out, s_ties;
-    const int tid = threadIdx.x;
+    __shared__ uint32_t sh[2], s_T;
+    __shared__ int s_count, s_more[2], s_bin, s_out, s_ties;
     // position in the visiting order: runs of 64 consecutive queries go to one XCD (they share clusters and hence
     // codes in that XCD's L2), successive runs to successive XCDs - a popular, large cluster (many queries, each
     // with much to score) is spread over all of them instead of making one XCD the last to finish
@@ -128,14 +157,20 @@ __global__ __launch_bounds__(256) void k_select_query(QuerySelectArgs a) {
     const int si = ((((slot >> rs) << 3) + (int)(blockIdx.x & 7)) << rs) + (slot & ((1 << rs) - 1));
     if (si >= a.nq) return;
     const int q = __builtin_amdgcn_readfirstlane(a.qorder[si]);     // uniform over the block: scalar loads below
-    const int w = a.w, m = a.m;
-    const bool l2 = a.sqnorm != nullptr, cols = a.pt_scale != nullptr, mixed = a.pt_first != nullptr;
-    if (tid == 0) s_count = 0;
+    const bool mixed = EXT && a.pt_first != nullptr;
+    if (tid == 0) { s_count = 0; s_more[0] = 0; s_more[1] = 0; s_T = 0u; }
     if (tid < w) {
-        const int pos = a.pos_of_slot[(size_t)q * w + tid];
-        ppos[tid] = pos;
+        const int pos = a.pos_of_slot[(size_t)q * w + tid], c = a.sel[(size_t)q * w + tid];
+        const int64_t r0 = a.off[c], r1 = a.off[c + 1];
+        const float s = a.sigma[pos];
         pk[tid] = a.pmax[pos];
+        ppos[tid] = pos;
+        prow[tid] = (int)r0; pcnt[tid] = (int)(r1 - r0);
+        psig[tid] = L2 ? 2.0f * s : s;
+        const float rf = mixed ? a.rho0[pos] : 0.0f;
+        prho[tid] = L2 ? 2.0f * rf : rf;
     }
+    for (int i = tid; i < kSelectBins; i += 256) bins[i] = 0;
     __syncthreads();
     if (tid < w) {      // order the pairs by best score, descending (ties: lower rank first)
         const uint32_t k = pk[tid];
@@ -145,104 +180,152 @@ __global__ __launch_bounds__(256) void k_select_query(QuerySelectArgs a) {
     }
     __syncthreads();
 
-    uint32_t T = 0u;          // running threshold key: the m-th best score seen so far (0: none yet)
-    int count = 0;            // entries in keys/rows, all >= T (uniform)
+    const uint32_t kmax = pk[order[0]];      // key of the best score of all
+    uint32_t T = 0u;          // running threshold key, at most the m-th best score seen so far (0: none yet)
+    float Tf = -INFINITY;     // the same as a score
     bool overflow = false;
+    int par = 0;
+    const int limit = cap - 4 * PIECE;       // a wavefront adds at most one piece after it has seen the count at or below this
 
-    // Tighten T to the m-th largest stored key and drop the entries below it (stable, in place).
-    auto compact = [&]() {
-        if (count < m) return;
-        int need_ties;
-        const uint32_t Tn = block_mth_largest(count, m, hist, sh, need_ties, [&](int i, uint32_t& key) { key = keys[i]; return true; });
+    // Keep the list's entries >= T only (stable, in place); returns how many.
+    auto filter = [&](int n) {
         int kept = 0;
-        for (int base = 0; base < count; base += 256) {
+        for (int base = 0; base < n; base += 256) {
             const int i = base + tid;
             uint32_t k = 0u;
             int32_t r = 0;
-            if (i < count) { k = keys[i]; r = rows[i]; }
-            const bool keep = i < count && k >= Tn;
+            if (i < n) { k = keys[i]; r = rows[i]; }
+            const bool keep = i < n && k >= T;
             int tot;
             const int rank = block_flag_scan<4>(keep, wsum, tot);     // barriers: the chunk is in registers before any write
             if (keep) { keys[kept + rank] = k; rows[kept + rank] = r; }
             kept += tot;
         }
         __syncthreads();
-        T = Tn;
-        count = kept;
         if (tid == 0) s_count = kept;
-        __syncthreads();
+        return kept;
+    };
+    // T from the bins: the far edge of the bin that holds the m-th best score seen (all four wavefronts meet around it).
+    auto read_bins = [&]() {
+        if (wv == 0) {
+            constexpr int PL = kSelectBins / 64;         // 28 consecutive bins per lane
+            int mine = 0;
+            const i32x4* b4 = reinterpret_cast<const i32x4*>(bins) + lane * (PL / 4);
+#pragma unroll
+            for (int j = 0; j < PL / 4; ++j) { const i32x4 h = b4[j]; mine += (h[0] + h[1]) + (h[2] + h[3]); }
+            int incl = mine;
+#pragma unroll
+            for (int o = 1; o < 64; o <<= 1) { const int t = __shfl_up(incl, o, 64); if (lane >= o) incl += t; }
+            // the lane whose run holds the m-th best; its bins are then looked through one per lane
+            const int src = __ffsll((unsigned long long)__ballot(incl >= m)) - 1;
+            const int cum = __builtin_amdgcn_readlane(incl - mine, src);
+            int x = lane < PL ? bins[src * PL + lane] : 0;
+#pragma unroll
+            for (int o = 1; o < 32; o <<= 1) { const int t = __shfl_up(x, o, 64); if (lane >= o) x += t; }
+            const int j = __ffsll((unsigned long long)__ballot(cum + x >= m)) - 1;
+            if (lane == 0) {
+                const uint32_t last = select_bin_last(src * PL + j);
+                s_bin = src * PL + j;
+                s_T = kmax > last ? kmax - last : 0u;
+            }
+        }
     };
 
-    // The codes of the PT points a thread scores between two capacity checks are requested together, with
-    // clamped addresses instead of branches, so that the loads overlap.
     for (int o = 0; o < w && !overflow; ++o) {
         const int jp = __builtin_amdgcn_readfirstlane(order[o]);
-        if (pk[jp] == 0u || pk[jp] < T) break;           // sorted: no later cluster can reach T either
-        const int c = a.sel[(size_t)q * w + jp];
-        const int64_t r0 = a.off[c];
-        const int m_c = (int)(a.off[c + 1] - r0);
-        const int pos = __builtin_amdgcn_readfirstlane(ppos[jp]);
-        // requests that do not depend on each other go out together: the pair's z and sigma, the first codes
-        const int zv = reinterpret_cast<const int*>(a.Z)[(size_t)pos * ZW + (tid < ZW ? tid : 0)];
-        const float s = a.sigma[pos];
-        const float rfirst = mixed ? a.rho0[pos] : 0.0f;
-        i32x4 code[PT][RB];
-        float bias[PT], psc[PT], pf[PT];
-        auto fetch_codes = [&](int p0) {
+        const uint32_t best = pk[jp];
+        if (best == 0u || best < T) break;               // sorted: no later cluster can reach T either (uniform)
+        const int m_c = __builtin_amdgcn_readfirstlane(pcnt[jp]), r0 = __builtin_amdgcn_readfirstlane(prow[jp]);
+        const float sp = psig[jp], r0p = prho[jp];
+        const i32x4* zp = reinterpret_cast<const i32x4*>(a.Z) + (size_t)__builtin_amdgcn_readfirstlane(ppos[jp]) * RB;
+        i32x4 zv[RB];                                    // (in flight with the first codes)
+#pragma unroll
+        for (int u = 0; u < RB; ++u) zv[u] = zp[u];
+        i32x4 code[3][PT][RB];
+        float bias[3][PT], psc[3][PT], pf[3][PT];
+        // clamped addresses instead of branches, so that the loads overlap (m_c > 0: the pair has a best score)
+        auto request = [&](int b, int piece) {
 #pragma unroll
             for (int e = 0; e < PT; ++e) {
-                {
-                    const int64_t row = r0 + min(p0 + e * 256 + tid, m_c - 1);
-                    const i32x4* bp = reinterpret_cast<const i32x4*>(a.Bp + (size_t)row * (RB * 16));
+                const size_t row = (size_t)r0 + min(piece * PIECE + e * 64 + lane, m_c - 1);
+                const i32x4* bp = reinterpret_cast<const i32x4*>(a.Bp) + row * RB;
 #pragma unroll
-                    for (int u = 0; u < RB; ++u) code[e][u] = bp[u];
-                    bias[e] = l2 ? a.sqnorm[row] : 0.0f;
-                    psc[e] = cols ? a.pt_scale[row] : 1.0f;     // times 1 is exact: one code path for both schemes
-                    pf[e] = mixed ? a.pt_first[row] : 0.0f;
-                }
+                for (int u = 0; u < RB; ++u) code[b][e][u] = bp[u];
+                if (L2) bias[b][e] = a.sqnorm[row];
+                if (EXT) { psc[b][e] = a.pt_scale[row]; pf[b][e] = mixed ? a.pt_first[row] : 0.0f; }
             }
         };
-        if (m_c > 0) fetch_codes(0);
-        __syncthreads();
-        if (tid < ZW) zw[tid] = zv;
-        __syncthreads();
-        const float sp = l2 ? 2.0f * s : s;
-        const float r0p = l2 ? 2.0f * rfirst : rfirst;
-        for (int p0 = 0; p0 < m_c; p0 += kQChunk) {
-            if (count > kQCap - kQChunk) {
-                compact();
-                if (count > kQCap - kQChunk) { overflow = true; break; }   // too many scores tie with the threshold
-            }
-            if (p0 > 0) fetch_codes(p0);
+        const int pieces = (m_c + PIECE - 1) / PIECE;
+        int piece = wv;
+        int z[ZW];                                       // uniform: scalar registers
+        for (;;) {
+            if (piece < pieces) {
+                request(0, piece);
+                request(1, piece + 4);
 #pragma unroll
-            for (int e = 0; e < PT; ++e) {
-                {
-                    const int t = p0 + e * 256 + tid;
-                    int y = 0;
+                for (int u = 0; u < ZW; ++u) z[u] = __builtin_amdgcn_readfirstlane(zv[u >> 2][u & 3]);
+                bool full = false;
+                while (piece < pieces && !full) {        // uniform over the wavefront
 #pragma unroll
-                    for (int u = 0; u < RB; ++u) {
-                        y = dot4_i8(code[e][u][0], zw[4 * u + 0], y);
-                        y = dot4_i8(code[e][u][1], zw[4 * u + 1], y);
-                        y = dot4_i8(code[e][u][2], zw[4 * u + 2], y);
-                        y = dot4_i8(code[e][u][3], zw[4 * u + 3], y);
-                    }
-                    float sc = __fmaf_rn((float)y, __fmul_rn(sp, psc[e]), -bias[e]);
-                    if (mixed) sc = __fmaf_rn(r0p, pf[e], sc);      // uniform
-                    const uint32_t key = float_key_asc(sc);
-                    if (t < m_c && key >= T) {
-                        const int at = atomicAdd(&s_count, 1);
-                        keys[at] = key;
-                        rows[at] = (int32_t)(r0 + t);
+                    for (int b = 0; b < 3; ++b) {
+                        if (piece < pieces && !full) {
+                            full = __builtin_amdgcn_readfirstlane(*(volatile int*)&s_count) > limit;
+                            if (!full) {
+                                request((b + 2) % 3, piece + 8);
+#pragma unroll
+                                for (int e = 0; e < PT; ++e) {
+                                    const int t = piece * PIECE + e * 64 + lane;
+                                    int y = 0;
+#pragma unroll
+                                    for (int u = 0; u < RB; ++u)
+#pragma unroll
+                                        for (int x = 0; x < 4; ++x) y = dot4_i8(code[b][e][u][x], z[4 * u + x], y);
+                                    float sc = __fmaf_rn((float)y, EXT ? __fmul_rn(sp, psc[b][e]) : sp, L2 ? -bias[b][e] : -0.0f);
+                                    if (EXT && mixed) sc = __fmaf_rn(r0p, pf[b][e], sc);
+                                    const bool in = t < m_c && !(sc < Tf);
+                                    const unsigned long long mk = __ballot(in);
+                                    if (mk) {
+                                        int base = 0;
+                                        if (lane == 0) base = atomicAdd(&s_count, __popcll(mk));
+                                        base = __builtin_amdgcn_readfirstlane(base);
+                                        if (in) {
+                                            const uint32_t key = float_key_asc(sc);
+                                            const int at = base + __popcll(mk & ((1ull << lane) - 1ull));
+                                            keys[at] = key;
+                                            rows[at] = r0 + t;
+                                            atomicAdd(&bins[select_bin(key < kmax ? kmax - key : 0u)], 1);
+                                        }
+                                    }
+                                }
+                                piece += 4;
+                            }
+                        }
                     }
                 }
             }
+            if (piece < pieces && lane == 0) s_more[par] = 1;
             __syncthreads();
-            count = s_count;
-            // every wavefront has read the counter before any adds the next chunk's arrivals to it: the block agrees
-            // on `count`, so on whether it compacts and on how many barriers that takes
-            if (p0 + kQChunk < m_c) __syncthreads();      // uniform
+            const int n = s_count;                       // (nothing is added before the next barrier)
+            const bool more = s_more[par] != 0;
+            if (tid == 0) s_more[par ^ 1] = 0;
+            if (n >= m) read_bins();                     // uniform
+            __syncthreads();
+            par ^= 1;
+            if (s_T > T) T = s_T;
+            if (n > limit) {                             // uniform
+                int left = filter(n);
+                if (left > limit) {                      // one bin holds too many: select exactly
+                    __syncthreads();
+                    int ties;
+                    T = block_mth_largest(left, m, hist, sh, ties, [&](int i, uint32_t& key) { key = keys[i]; return true; });
+                    left = filter(left);
+                }
+                __syncthreads();
+                if (left > limit) { overflow = true; break; }     // too many scores tie with the threshold
+            }
+            Tf = T > 0x007fffffu ? key_to_float(T) : -INFINITY;
+            if (!more) break;
         }
-        if (!overflow) compact();     // new scores arrived: raise the threshold before looking at the next cluster
     }
 
     int32_t* out = a.cand + (size_t)q * m;
@@ -259,40 +342,66 @@ __global__ __launch_bounds__(256) void k_select_query(QuerySelectArgs a) {
     if (overflow) {
         if (tid == 0) {
             a.fb_list[atomicAdd(a.fb_count, 1)] = q; a.n_kept[q] = -1; a.tau[q] = key_to_float(T);
-            a.qkey[q] = (int32_t)a.off[a.sel[(size_t)q * w + order[0]]];     // first row of its most promising cluster
+            a.qkey[q] = prow[order[0]];                  // first row of its most promising cluster
         }
         return;
     }
-    if (tid == 0) { a.n_kept[q] = count; a.tau[q] = count >= m ? key_to_float(T) : -INFINITY; s_out = 0; s_ties = 0; }
-    if (count <= m) {       // every kept score is a candidate (count < m: all scored points)
-        int mn = 0x7fffffff;
+    const int count = s_count;
+    int mn = 0x7fffffff;
+    if (count < m) {        // every scored point is a candidate
+        if (tid == 0) { a.n_kept[q] = count; a.tau[q] = -INFINITY; }
         for (int i = tid; i < m; i += 256) { const int r = i < count ? rows[i] : -1; out[i] = r; if (r >= 0) mn = min(mn, r); }
-        block_min_to(a.qkey + q, mn, &s_ties);
+        block_min_to(a.qkey + q, mn, hist);
         return;
     }
-    // count > m: T is the m-th largest key (compact() ran after the last arrivals); ties at T go to the lower rows
+    // The m-th best score lies in bin s_bin: entries of nearer bins are candidates, the bin's own are ranked (score descending,
+    // row ascending).  Entries below T - an exact selection may have raised it into the bin - are none.
+    const int bin = s_bin;
+    const uint32_t dist0 = select_bin_first(bin), near = bin == 0 ? 0xffffffffu : kmax - dist0;       // keys of the bin: T .. near
     __syncthreads();
-    int above = 0;
-    for (int i = tid; i < count; i += 256) above += keys[i] > T ? 1 : 0;
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) above += __shfl_xor(above, o, 64);
-    if ((tid & 63) == 0) atomicAdd(&s_out, above);
+    if (tid == 0) { s_out = 0; s_ties = 0; a.n_kept[q] = count; }
     __syncthreads();
-    const int n_above = s_out;
-    const int need_ties = m - n_above;
-    __syncthreads();
-    if (tid == 0) s_out = 0;
-    int dummy;
-    const uint32_t RT = block_mth_largest(count, need_ties, hist, sh, dummy,
-                                          [&](int i, uint32_t& key) { key = ~(uint32_t)rows[i]; return keys[i] == T; });
-    int mn = 0x7fffffff;
-    for (int i = tid; i < count; i += 256) {
-        const uint32_t key = keys[i];
-        if (key > T) { out[atomicAdd(&s_out, 1)] = rows[i]; mn = min(mn, rows[i]); }
-        else if ((~(uint32_t)rows[i]) >= RT) { out[n_above + atomicAdd(&s_ties, 1)] = rows[i]; mn = min(mn, rows[i]); }
+    uint32_t* bkey = reinterpret_cast<uint32_t*>(bins);
+    int32_t* brow = reinterpret_cast<int32_t*>(bins) + 256;
+    for (int i0 = 0; i0 < count; i0 += 256) {            // uniform
+        const int i = i0 + tid;
+        const uint32_t k = i < count ? keys[i] : 0u;
+        const int32_t r = i < count ? rows[i] : 0;
+        const bool above = k > near, member = k >= T && k <= near && k != 0u;
+        const unsigned long long ma = __ballot(above), mb = __ballot(member);
+        int ba = 0, bb = 0;
+        if (lane == 0) { if (ma) ba = atomicAdd(&s_out, __popcll(ma)); if (mb) bb = atomicAdd(&s_ties, __popcll(mb)); }
+        ba = __builtin_amdgcn_readfirstlane(ba); bb = __builtin_amdgcn_readfirstlane(bb);
+        const unsigned long long below = (1ull << lane) - 1ull;
+        if (above) { out[ba + __popcll(ma & below)] = r; mn = min(mn, r); }
+        if (member) { const int at = bb + __popcll(mb & below); if (at < 256) { bkey[at] = k; brow[at] = r; } }
     }
     __syncthreads();
-    block_min_to(a.qkey + q, mn, &s_out);
+    const int n_above = s_out, nb = s_ties, need = m - n_above;
+    if (nb <= 256) {                                     // uniform
+        if (tid < nb) {
+            const uint32_t k = bkey[tid];
+            const int32_t r = brow[tid];
+            int rank = 0;
+            for (int u = 0; u < nb; ++u) rank += (bkey[u] > k || (bkey[u] == k && brow[u] < r)) ? 1 : 0;
+            if (rank < need) { out[n_above + rank] = r; mn = min(mn, r); }
+            if (rank == need - 1) a.tau[q] = key_to_float(k);
+        }
+    } else {
+        // a long run of (nearly) equal scores: radix selection of the need-th best key of the bin, ties to the lower rows
+        int ties, dummy;
+        const uint32_t KT = block_mth_largest(count, need, hist, sh, ties, [&](int i, uint32_t& key) { key = keys[i]; return keys[i] >= T && keys[i] <= near; });
+        const uint32_t RT = block_mth_largest(count, ties, hist, sh, dummy, [&](int i, uint32_t& key) { key = ~(uint32_t)rows[i]; return keys[i] == KT; });
+        if (tid == 0) { s_out = n_above; a.tau[q] = key_to_float(KT); }
+        __syncthreads();
+        for (int i = tid; i < count; i += 256) {
+            const uint32_t k = keys[i];
+            if (k > near || k < KT || (k == KT && (~(uint32_t)rows[i]) < RT)) continue;
+            out[atomicAdd(&s_out, 1)] = rows[i];
+            mn = min(mn, rows[i]);
+        }
+    }
+    block_min_to(a.qkey + q, mn, hist);
 }
 
 }  // namespace lorann

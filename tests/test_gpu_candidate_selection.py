@@ -41,3 +41,33 @@ def test_clusters_of_many_chunks(B, metric, m):
         _, _, st = gix.search_stages(q, 5, 3, m)
         np.testing.assert_array_equal(np.sort(st["cand_rows"].astype(np.int64), axis=1), np.sort(ost["cand_rows"], axis=1))
     gix.close()
+
+
+@pytest.mark.parametrize("scheme", ["cluster", "columns", "mixed"])
+@pytest.mark.parametrize("metric,r,m,nq", [(0, 16, 200, 2049), (1, 40, 10, 2100), (1, 24, 352, 2060), (2, 64, 353, 2050), (0, 32, 864, 2051), (1, 8, 865, 2049),
+                                           (1, 24, 200, 300), (0, 48, 600, 2048)])
+def test_one_cluster_holds_most_points(B, metric, r, m, nq, scheme):
+    """A cluster of 41 111 points (81 work items, the last one ragged) beside small and empty ones: most of it is dismissed by the
+    best scores of its quarters (batches beyond 2048 queries and m up to 864; below and above four wavefronts share a query).  Half of its points repeat the codes of the other half, so scores tie at every threshold."""
+    ix = _index(metric, n=48_000, L=7, r=r, seed=11 + r)
+    rng = np.random.default_rng(r)
+    ix.cluster_offsets[:] = torch.tensor([0, 1500, 1500, 42_611, 44_700, 46_749, 46_750, 48_000])
+    ix.B[1500 + 20_000:1500 + 40_000] = ix.B[1500:1500 + 20_000]
+    if metric == 1:
+        ix.corpus[1500 + 20_000:1500 + 40_000] = ix.corpus[1500:1500 + 20_000]
+    if scheme != "cluster":
+        ix.scale_A_columns = torch.from_numpy(rng.uniform(0.5, 2.0, (7, r)).astype(np.float32)) * 1e-3
+        ix.scale_B_points = torch.ones(48_000)
+        ix.scale_B_points[::3] = 1.25
+    if scheme == "mixed":
+        ix.first_row_A = torch.from_numpy(rng.normal(size=(7, r)).astype(np.float32))
+        ix.first_row_B = torch.from_numpy((rng.integers(-3, 4, 48_000) / 4).astype(np.float32))
+    queries = rng.standard_normal((nq, 32)).astype(np.float32)
+    gix = B.Index.from_arrays(ix.to("cuda"))
+    _, _, st = gix.search_stages(torch.from_numpy(queries).cuda(), 5, 5, m)
+    some = np.concatenate([np.arange(0, nq, 16), np.arange(nq - 5, nq)])         # (the oracle on the CPU: a sample)
+    _, _, ost = O.search(O.OracleIndex(ix.numpy()), queries[some], 5, 5, m, stages=True)
+    st = {f: st[f][some] for f in ("cand_rows", "pmax")}
+    np.testing.assert_array_equal(np.sort(st["cand_rows"].astype(np.int64), axis=1), np.sort(ost["cand_rows"], axis=1))
+    np.testing.assert_array_equal(st["pmax"], ost["pair_best"])
+    gix.close()
