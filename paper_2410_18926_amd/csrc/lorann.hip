@@ -340,7 +340,7 @@ void launch_pair_max(lorann_index* ix, Workspace& ws, hipStream_t s, int64_t npa
 #define LAUNCH_PM4(KS_, L2_, COLS_, MIX_, DUMP_)                                                                      \
     do {                                                                                                             \
         if (stream) hipLaunchKernelGGL((k_pair_max<1, KS_, L2_, 8 / KS_, true, 4, COLS_, MIX_, DUMP_>), gs, dim3(256), 0, s, sc); \
-        else hipLaunchKernelGGL((k_pair_max<kNZ, KS_, L2_, 4, false, 4, COLS_, MIX_, DUMP_>), gp, dim3(256), 0, s, sc); \
+        else hipLaunchKernelGGL((k_pair_max<kNZ, KS_, L2_, (L2_ || COLS_) ? 2 : 4, false, 4, COLS_, MIX_, DUMP_>), gp, dim3(256), 0, s, sc); \
     } while (0)
 #define LAUNCH_PM3(KS_, L2_, DUMP_)                                                                                   \
     do {                                                                                                             \

@@ -165,7 +165,9 @@ __global__ __launch_bounds__(64 * WPB) void k_pair_max(ScoreArgs a) {
                     const bool has2 = t + 1 < ntiles;                              // uniform
                     const bool full = has2 && 32 * t + 64 <= m_c;                  // uniform: both tiles complete
                     const bool ok_a = 32 * t + j < m_c, ok_b = has2 && 32 * (t + 1) + j < m_c;
-                    const float bias_a = L2 ? nb[u] : 0.0f, bias_b = L2 ? nb[u + 1] : 0.0f;
+                    // what is added to a scaled product: minus the point's bias; minus infinity where the tile has no point (one
+                    // selection per tile instead of one per score)
+                    const float off_a = ok_a ? (L2 ? -nb[u] : -0.0f) : -INFINITY, off_b = ok_b ? (L2 ? -nb[u + 1] : -0.0f) : -INFINITY;
 #pragma unroll
                     for (int z = 0; z < NZ; ++z) {
                         i32x16 acc_a = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0}, acc_b = acc_a;
@@ -196,15 +198,13 @@ __global__ __launch_bounds__(64 * WPB) void k_pair_max(ScoreArgs a) {
                         } else {
 #pragma unroll
                             for (int v = 0; v < 16; ++v) {
-                                const float mult_a = COLS ? __fmul_rn(sgv[z][v], ns[u]) : sgv[z][v];
-                                const float mult_b = COLS ? __fmul_rn(sgv[z][v], ns[u + 1]) : sgv[z][v];
-                                float sc_a = __fmaf_rn((float)acc_a[v], mult_a, -bias_a);
-                                float sc_b = __fmaf_rn((float)acc_b[v], mult_b, -bias_b);
+                                float sc_a = __fmaf_rn((float)acc_a[v], COLS ? __fmul_rn(sgv[z][v], ns[u]) : sgv[z][v], off_a);
+                                float sc_b = __fmaf_rn((float)acc_b[v], COLS ? __fmul_rn(sgv[z][v], ns[u + 1]) : sgv[z][v], off_b);
                                 if (MIX) {
                                     sc_a = __fmaf_rn(r0v[MIX ? z : 0][v], nf[u], sc_a);
                                     sc_b = __fmaf_rn(r0v[MIX ? z : 0][v], nf[u + 1], sc_b);
                                 }
-                                mxf[z][v] = fmaxf(fmaxf(mxf[z][v], ok_a ? sc_a : -INFINITY), ok_b ? sc_b : -INFINITY);
+                                mxf[z][v] = fmaxf(fmaxf(mxf[z][v], sc_a), sc_b);
                             }
                         }
                     }
