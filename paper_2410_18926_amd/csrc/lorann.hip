@@ -723,10 +723,10 @@ int search_chunk(lorann_index* ix, Workspace& ws, hipStream_t s, const float* dQ
 #define LAUNCH_SA(RT_, RES_)                                                                                   \
     do {                                                                                                       \
         if (ix->sA_cols) hipLaunchKernelGGL((k_stage_a<RT_, RES_, true>), grid, dim3(256), 0, s, ws.q8.as<int8_t>(), ws.dx.as<float>(), ix->A, ix->sA_cols, ix->sB, \
-                                            ws.bucket_off.as<int32_t>(), ws.tile_off.as<int32_t>(), tpw, (int)(npairs / 16 + L / 2), ws.slot_of_pos.as<int32_t>(), L, dp, ix->r, w, ws.Z.as<int8_t>(), ws.sigma.as<float>(), \
+                                            ws.bucket_off.as<int32_t>(), ws.tile_off.as<int32_t>(), tpw, (int)(npairs / 16 + L / 2), ws.slot_of_pos.as<int32_t>(), L, dp, ix->r, w, slot_division_magic(w), ws.Z.as<int8_t>(), ws.sigma.as<float>(), \
                                             qp, (const float*)ix->A_first, mixed ? ws.rho0.as<float>() : (float*)nullptr); \
         else hipLaunchKernelGGL((k_stage_a<RT_, RES_, false>), grid, dim3(256), 0, s, ws.q8.as<int8_t>(), ws.dx.as<float>(), ix->A, ix->sA, ix->sB, \
-                                ws.bucket_off.as<int32_t>(), ws.tile_off.as<int32_t>(), tpw, (int)(npairs / 16 + L / 2), ws.slot_of_pos.as<int32_t>(), L, dp, ix->r, w, ws.Z.as<int8_t>(), ws.sigma.as<float>(), \
+                                ws.bucket_off.as<int32_t>(), ws.tile_off.as<int32_t>(), tpw, (int)(npairs / 16 + L / 2), ws.slot_of_pos.as<int32_t>(), L, dp, ix->r, w, slot_division_magic(w), ws.Z.as<int8_t>(), ws.sigma.as<float>(), \
                                 (const float*)nullptr, (const float*)nullptr, (float*)nullptr); \
     } while (0)
         if (r_pad == 32) { if (dp <= 256) LAUNCH_SA(2, true); else LAUNCH_SA(2, false); }

@@ -14,6 +14,21 @@ namespace lorann {
 
 __device__ __forceinline__ i32x4 load16(const int8_t* p) { return *reinterpret_cast<const i32x4*>(p); }
 
+// Maximum over each row of 16 lanes, in every lane of the row (rotations inside the row, no LDS traffic).
+__device__ __forceinline__ uint32_t row16_max_u32(uint32_t v) {
+    auto turned = [](uint32_t x, auto ctrl) { return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, decltype(ctrl)::value, 0xf, 0xf, true); };
+    v = max(v, turned(v, std::integral_constant<int, 0x128>{}));     // row_ror:8, 4, 2, 1
+    v = max(v, turned(v, std::integral_constant<int, 0x124>{}));
+    v = max(v, turned(v, std::integral_constant<int, 0x122>{}));
+    v = max(v, turned(v, std::integral_constant<int, 0x121>{}));
+    return v;
+}
+
+// slot / w by a multiplication: magic = ceil(2^32 / w).  Exact while slot * (magic * w - 2^32) < 2^32; the second factor is below w <= 256,
+// and a launch has at most 2^15 * 256 slots.
+inline uint32_t slot_division_magic(int w) { return (uint32_t)(((uint64_t(1) << 32) + (uint64_t)w - 1) / (uint64_t)w); }
+__device__ __forceinline__ int query_of_slot(int slot, int w, uint32_t magic) { return w == 1 ? slot : (int)__umulhi((uint32_t)slot, magic); }
+
 // Find c with off[c] <= t < off[c+1] (off non-decreasing, off[0] = 0, t < off[L]).
 __device__ __forceinline__ int find_bucket(const int32_t* __restrict__ off, int L, int t) {
     int lo = 0, hi = L;   // invariant: off[lo] <= t < off[hi]
@@ -72,7 +87,7 @@ __global__ __launch_bounds__(256) void k_stage_a(const int8_t* __restrict__ q8, 
                                                   const float* __restrict__ sB, const int32_t* __restrict__ bucket_off,
                                                   const int32_t* __restrict__ tile_off, int tpw, int tiles_guess,
                                                   const int32_t* __restrict__ slot_of_pos,
-                                                  int L, int dp, int r, int w, int8_t* __restrict__ Z, float* __restrict__ sigma,
+                                                  int L, int dp, int r, int w, uint32_t w_magic, int8_t* __restrict__ Z, float* __restrict__ sigma,
                                                   const float* __restrict__ qproj = nullptr, const float* __restrict__ A_first = nullptr,
                                                   float* __restrict__ rho0 = nullptr) {
     const int lane = threadIdx.x & 63;
@@ -118,13 +133,25 @@ __global__ __launch_bounds__(256) void k_stage_a(const int8_t* __restrict__ q8, 
     for (int tile = first; tile < last; ++tile) {
     const int base = pbeg + tile * 16;
     const bool row_ok = base + i < end;
-    const int8_t* qrow = q8 + (size_t)(slot_next / w) * dp;
+    const int8_t* qrow = q8 + (size_t)query_of_slot(slot_next, w, w_magic) * dp;
+    // what the epilogue needs of the pairs is requested here, not where it is used: two dependent round trips per row otherwise
+    // (lane i < 4 of row group g: pair 4 g + i)
+    int eslot[COLS ? 4 : 1];
+#pragma unroll
+    for (int v = 0; v < (COLS ? 4 : 1); ++v) eslot[v] = slot_of_pos[min(base + 4 * g + (COLS ? v : (i & 3)), end - 1)];
     // the next tile's pair numbers are requested now, its query rows when this tile is done
     slot_next = slot_of_pos[min(base + 16 + i, end - 1)];
 
     i32x4 acc[RT];
 #pragma unroll
     for (int t = 0; t < RT; ++t) acc[t] = zero4;
+    float edx[COLS ? 4 : 1], ex0[COLS ? 4 : 1];
+#pragma unroll
+    for (int v = 0; v < (COLS ? 4 : 1); ++v) {
+        const int qv = query_of_slot(eslot[v], w, w_magic);
+        edx[v] = dx[qv];
+        ex0[v] = COLS && A_first != nullptr ? qproj[(size_t)qv * dp] : 0.0f;
+    }
 
     for (int s0 = 0; s0 < steps; s0 += SB) {
         i32x4 av[SB], bload[RES ? 1 : SB][RT];
@@ -156,9 +183,7 @@ __global__ __launch_bounds__(256) void k_stage_a(const int8_t* __restrict__ q8, 
 #pragma unroll
         for (int v = 0; v < 4; ++v) {
             const int pos = base + 4 * g + v;
-            const int qv = slot_of_pos[min(pos, end - 1)] / w;
-            const float dxq = dx[qv];
-            const float x0 = mixed ? qproj[(size_t)qv * dp] : 0.0f;
+            const float dxq = edx[v], x0 = ex0[v];
             float rho[RT], mx = 0.0f;
 #pragma unroll
             for (int t = 0; t < RT; ++t) {
@@ -172,8 +197,7 @@ __global__ __launch_bounds__(256) void k_stage_a(const int8_t* __restrict__ q8, 
                 }
                 mx = fmaxf(mx, fabsf(rho[t]));
             }
-#pragma unroll
-            for (int o = 1; o < 16; o <<= 1) mx = fmaxf(mx, __shfl_xor(mx, o, 64));
+            mx = __uint_as_float(row16_max_u32(__float_as_uint(mx)));      // (non-negative: ordered like its bits; a NaN counts as the largest)
             if (pos < end) {
                 const bool any = mx > 0.0f;
                 const float cx = any ? (float)(127.0 / (double)mx) : 0.0f;
@@ -188,35 +212,34 @@ __global__ __launch_bounds__(256) void k_stage_a(const int8_t* __restrict__ q8, 
         }
         continue;
     }
+    uint32_t mxs = 0u;                                   // lane i < 4: the maximum of row 4 g + i
 #pragma unroll
     for (int v = 0; v < 4; ++v) {
         uint32_t mx = 0;
 #pragma unroll
         for (int t = 0; t < RT; ++t) mx = max(mx, (uint32_t)abs(acc[t][v]));
-#pragma unroll
-        for (int o = 1; o < 16; o <<= 1) mx = max(mx, (uint32_t)__shfl_xor((int)mx, o, 64));
+        mx = row16_max_u32(mx);
+        mxs = i == v ? mx : mxs;
+        // (254 a + mx) / (2 mx): the quotient (at most 127) from a float product, off by one at most, corrected by its remainder
+        const uint32_t den = max(2u * mx, 1u);
+        const float inv = __builtin_amdgcn_rcpf((float)den);
         const int pos = base + 4 * g + v;
         if (pos < end) {
 #pragma unroll
             for (int t = 0; t < RT; ++t) {
-                int zc = 0;
-                if (mx != 0u) {
-                    const int R = acc[t][v];
-                    const uint32_t a = (uint32_t)abs(R);
-                    const uint32_t q = (254u * a + mx) / (2u * mx);   // < 2^32 because d' <= 1024
-                    zc = R < 0 ? -(int)q : (int)q;
-                }
-                Z[(size_t)pos * (RT * 16) + t * 16 + i] = (int8_t)zc;
-            }
-            if (i == 0) {
-                float s = 0.0f;
-                if (mx != 0u) {
-                    const int qi = slot_of_pos[pos] / w;
-                    s = (float)((double)mx / 127.0 * (double)dx[qi] * (double)sA[c] * (double)sB[c]);
-                }
-                sigma[pos] = s;
+                const int R = acc[t][v];
+                const uint32_t num = 254u * (uint32_t)abs(R) + mx;        // < 2^32 because d' <= 1024
+                uint32_t q = (uint32_t)((float)num * inv);
+                const int32_t rem = (int32_t)(num - q * den);             // -den <= rem < 2 den < 2^27 (the exact quotient has 0 <= rem < den)
+                q = rem < 0 ? q - 1u : rem >= (int32_t)den ? q + 1u : q;
+                Z[(size_t)pos * (RT * 16) + t * 16 + i] = (int8_t)(R < 0 ? -(int)q : (int)q);
             }
         }
+    }
+    {
+        const int pos = base + 4 * g + i;
+        if (i < 4 && pos < end)
+            sigma[pos] = mxs != 0u ? (float)((double)mxs / 127.0 * (double)edx[0] * (double)sA[c] * (double)sB[c]) : 0.0f;
     }
     }   // tiles of this cluster
     }   // clusters of this wavefront
