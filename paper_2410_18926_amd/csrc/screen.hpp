@@ -487,6 +487,18 @@ __global__ __launch_bounds__(256) void k_select_clusters_screen_wave(ScreenArgs 
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
     };
     const unsigned long long below = (1ull << lane) - 1ull;
+    // The w-th smallest key, its last nine bits cleared (with them set it is a threshold a little too large: as safe, and the list
+    // grows by next to nothing); smaller(probe): how many keys are below it.  Bit by bit, a ballot each: ranking 64 to 128 entries by
+    // counting 64-bit words was half of this kernel's instructions.
+    auto wth = [&](auto smaller) {
+        uint32_t k = 0u;
+#pragma unroll
+        for (int b = 31; b >= 9; --b) {
+            const uint32_t probe = k | (1u << b);
+            if (smaller(probe) < w) k = probe;           // uniform
+        }
+        return k;
+    };
     int c2 = 0;
     bool listed = false;
     if (w <= 64) {
@@ -496,21 +508,7 @@ __global__ __launch_bounds__(256) void k_select_clusters_screen_wave(ScreenArgs 
         uint32_t mn = 0xFFFFFFFFu;
 #pragma unroll
         for (int i = 0; i < KPL; ++i) mn = min(mn, key[i]);
-        const unsigned long long mine = ((unsigned long long)mn << 32) | (unsigned)lane;
-        cand[lane] = mine;
-        lds_sync();
-        int rank = 0;
-        {
-            const ulonglong2* t2 = reinterpret_cast<const ulonglong2*>(cand);
-#pragma unroll 8
-            for (int u = 0; u < 32; ++u) {
-                const ulonglong2 t = t2[u];
-                rank += (t.x < mine ? 1 : 0) + (t.y < mine ? 1 : 0);
-            }
-        }
-        const int src = __ffsll((unsigned long long)__ballot(rank == w - 1)) - 1;     // exactly one lane
-        const float tf1 = widen(key_to_float((uint32_t)__shfl((int)mn, src, 64)));
-        lds_sync();
+        const float tf1 = widen(key_to_float(wth([&](uint32_t probe) { return __popcll(__ballot(mn < probe)); }) | 511u));
         int c1 = 0;
 #pragma unroll
         for (int i = 0; i < KPL; ++i) {
@@ -524,26 +522,20 @@ __global__ __launch_bounds__(256) void k_select_clusters_screen_wave(ScreenArgs 
         if (c1 <= kScreenWaveCap) {                        // uniform
             if (lane < 2) cand[c1 + lane] = ~0ull;
             lds_sync();
-            const ulonglong2* cc = reinterpret_cast<const ulonglong2*>(cand);
-            const int c_pairs = (c1 + 1) >> 1;
-            uint32_t gw_mine = 0u;
-            bool found = false;
             unsigned long long mine_e[kScreenWaveCap / 64];
 #pragma unroll
             for (int j = 0; j < kScreenWaveCap / 64; ++j) {
                 const int e = lane + 64 * j;
                 mine_e[j] = e < c1 ? cand[e] : ~0ull;
-                int r = 0;
-                if (e < c1) {
-                    for (int u = 0; u < c_pairs; ++u) {
-                        const ulonglong2 t = cc[u];
-                        r += (t.x < mine_e[j] ? 1 : 0) + (t.y < mine_e[j] ? 1 : 0);
-                    }
-                    if (r == w - 1) { found = true; gw_mine = (uint32_t)(mine_e[j] >> 32); }
-                }
             }
-            const int src2 = __ffsll((unsigned long long)__ballot(found)) - 1;
-            const float tf2 = widen(key_to_float((uint32_t)__shfl((int)gw_mine, src2, 64)));
+            const float tf2 = widen(key_to_float(wth([&](uint32_t probe) {
+                int c = 0;
+#pragma unroll
+                for (int j = 0; j < kScreenWaveCap / 64; ++j)
+                    if (64 * j < c1) c += __popcll(__ballot((uint32_t)(mine_e[j] >> 32) < probe));      // uniform (beyond the list: the largest key)
+                return c;
+            }) | 511u));
+            lds_sync();
 #pragma unroll
             for (int j = 0; j < kScreenWaveCap / 64; ++j) {
                 const int e = lane + 64 * j;
@@ -580,6 +572,12 @@ __global__ __launch_bounds__(256) void k_select_clusters_screen_wave(ScreenArgs 
     const int grp = lane >> 4, l16 = lane & 15;
     const int n_exact = all_exact ? L : c2;
     const float4* q4 = reinterpret_cast<const float4*>(qs);
+    double xq[4][4];                                     // d' <= 256: this lane's share of the query, widened once
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+        const float4 x = q4[min(l16 + 16 * u, d4 - 1)];
+        xq[u][0] = (double)x.x; xq[u][1] = (double)x.y; xq[u][2] = (double)x.z; xq[u][3] = (double)x.w;
+    }
     auto exact_of = [&](int l, const float4* mu) {       // full rows of 16 lanes execute this together
         double acc = 0.0;
         for (int i4 = l16; i4 < d4; i4 += 16) {
@@ -611,11 +609,10 @@ __global__ __launch_bounds__(256) void k_select_clusters_screen_wave(ScreenArgs 
 #pragma unroll
                 for (int u = 0; u < 4; ++u) {
                     if (l16 + 16 * u < d4) {
-                        const float4 x = q4[l16 + 16 * u];
-                        acc += (double)x.x * (double)m[r][u].x;
-                        acc += (double)x.y * (double)m[r][u].y;
-                        acc += (double)x.z * (double)m[r][u].z;
-                        acc += (double)x.w * (double)m[r][u].w;
+                        acc += xq[u][0] * (double)m[r][u].x;
+                        acc += xq[u][1] * (double)m[r][u].y;
+                        acc += xq[u][2] * (double)m[r][u].z;
+                        acc += xq[u][3] * (double)m[r][u].w;
                     }
                 }
                 acc = row16_sum_f64_last(acc);
