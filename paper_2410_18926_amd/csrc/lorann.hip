@@ -502,10 +502,13 @@ int launch_screened_rerank(lorann_index* ix, Workspace& ws, hipStream_t s, const
     ra.rel_err = (half_rows ? hs.rel_lost : hs.rel_err) * 1.0001f;
     ra.rel_norm = half_rows ? 1.0001f * hs.rel_round * (2.0f + hs.rel_round) : 0.0f;
     ra.nscale = half_rows ? 1.0001f * (1.0f + hs.rel_round) : 1.0001f;
-    // blocks of a few tiles per wavefront: enough of them to fill the machine several times over
+    // Enough blocks to fill the machine several times over, and twice as many where a block still has 128 KiB of rows or so to read
+    // (half of the candidates are shared): 2 KB rows 783 -> 718 us with 9 blocks per group instead of 5, 768-byte rows at 10M points
+    // 2126 -> 2079, but 256-byte rows 74 -> 91.
     ra.slices = 1;
     const int max_slices = std::min(16, (pl.screen_gq * m + 63) / 64);
-    while ((int64_t)ra.slices * pl.ngroups < 4096 && ra.slices < max_slices) ++ra.slices;
+    const int64_t group_bytes = (int64_t)pl.screen_gq * m * ix->ld_h;
+    while (ra.slices < max_slices && (ra.slices * pl.ngroups < 4096 || (ra.slices * pl.ngroups < 8192 && group_bytes / (ra.slices + 1) >= (128 << 10)))) ++ra.slices;
     ws.last_ngroups = pl.ngroups;
     {
         Prof p(ix, K_UNION, s);
