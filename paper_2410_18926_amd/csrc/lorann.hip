@@ -415,6 +415,12 @@ ChunkPlan plan_chunk(const lorann_index* ix, int64_t nq, int k, int w, int m, bo
     // bound by the latency of the three launches, where the grouped re-rank's are shorter (64 queries: 115 us against 118).
     const int ld = half_stride(ix->d);
     pl.screen_gq = std::min(pl.small ? 1 : screen_group_size(m), (64 * 1024) / (2 * ld + 16));
+    // With few queries per cluster (nq <= 2 L) the queries of a group hardly share rows: 16 of them fill the union's table to 0.8 with
+    // distinct rows, and a few dozen such blocks are one long chain of probes.  As few queries as keep all union blocks resident (four
+    // per CU), at least 4: union 41 -> 16 us and gather 42 -> 43 at 1024 queries over 16 384 clusters, 50 -> 23 and 134 -> 130 at
+    // 4096; 1024 over 1024 42 -> 17, 59 -> 61.  Not beyond: 1000 queries over 64 clusters 14 -> 12, but 10 -> 13 for twice the rows;
+    // 16 384 queries over 16 384 clusters in groups of 4 lose (51 -> 69).
+    if (!pl.small && nq <= 2 * (int64_t)L) pl.screen_gq = (int)std::min<int64_t>(pl.screen_gq, std::max<int64_t>(4, (nq + 1023) / 1024));
     pl.screened = allow_screened && ix->rerank_mode != LORANN_RERANK_NONE && !ix->force_exact && !(pl.small && pl.grouped) && ix->corpus_h && pl.screen_gq > 0 && 4 * k <= m;
     pl.screen_stride = (pl.screen_gq * m + 15) & ~15;
     if (pl.screened) pl.grouped = false;

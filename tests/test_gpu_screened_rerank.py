@@ -80,3 +80,20 @@ def test_queries_that_are_no_numbers_keep_every_candidate(B):
     np.testing.assert_array_equal(ids[50:52], e_ids)
     np.testing.assert_array_equal(dist[50:52], e_d)
     gix.close()
+
+
+@pytest.mark.parametrize("nq", [65, 67, 400, 401, 4097, 5003])
+def test_few_queries_per_cluster(B, nq):
+    """Up to two queries per cluster the groups are smaller (4 queries; 5 from 4097 on where the clusters are that many): batches
+    that end inside a group and on both sides of the rule, against the plain re-rank."""
+    L = 2600 if nq > 4000 else 200
+    rng = np.random.default_rng(nq)
+    ix = _random_index(rng, n=9000, d=48, L=L, r=8, metric=nq % 3, dp=32)
+    q = rng.normal(size=(nq, 48)).astype(np.float32)
+    gix = B.Index(**ix)
+    s_ids, s_d = gix.search(q, 10, 40, 100)
+    gix.set_exact_selection(True)
+    e_ids, e_d = gix.search(q, 10, 40, 100)
+    np.testing.assert_array_equal(s_ids, e_ids)
+    np.testing.assert_array_equal(s_d, e_d)
+    gix.close()
