@@ -87,15 +87,17 @@ def kernel_models(wl, nq, touched_rows, npairs, scores, column_scales=False, mix
         "stage_a_i8": lat, "select_query": lat, "order_queries": lat, "group_union": lat, "topk": lat,
         "score_select_exact": lat, "candidate_scores": lat,
         "pair_max_i8": pm,
-        "rerank": ("hbm", nq * m * d * 4 / 1e9, PEAK_HBM_GBS, "GB/s"),     # algorithmic; the headline uses the bytes the kernel requests
+        "rerank": ("hbm", nq * m * d * 4 / 1e9, PEAK_HBM_GBS, "GB/s"),     # algorithmic; replaced by the bytes the kernel requests
     }
 
 
 def gather_accounting(gix, wl, queries, k, w, m, elem_bytes):
     """Bytes of the re-rank gather for one batch, taken from this run (lane 0, synchronous):
       algorithmic  every query gathers its m rows (the method as stated, Sec. 2.2): nq * m * d * elem
-      requested    what the kernel asks the memory system for: each row once per GROUP of queries that share it
-                   (sum over groups of their distinct rows), the queries, the row lists and the results
+      requested    what the gather asks the memory system for: each row once per GROUP of queries that share it
+                   (sum over groups of their distinct rows), the queries, the row lists and the results.  With k <= m / 4 the
+                   gather is the screening one: it reads the library's binary16 copy of the rows, whatever the rows that the
+                   few survivors are read from
       floor        each distinct candidate row of the whole batch once - no kernel can read less."""
     nq, d = queries.shape[0], wl.d
     st = gix.search_stages(queries, k, w, m)[2]
@@ -103,9 +105,18 @@ def gather_accounting(gix, wl, queries, k, w, m, elem_bytes):
     valid = int((cand >= 0).sum())
     distinct = int(np.unique(cand[cand >= 0]).size)
     union_rows = gix.profile_gather_rows()
-    acc = {"algorithmic_bytes": nq * m * d * elem_bytes, "floor_bytes": distinct * d * elem_bytes,
-           "candidate_rows": valid, "distinct_rows": distinct, "rows_fetched": union_rows if union_rows >= 0 else None}
-    if union_rows >= 0:
+    screened = union_rows >= 0 and 4 * k <= m
+    algorithmic = nq * m * d * elem_bytes
+    if screened:
+        elem_bytes = 2
+    acc = {"algorithmic_bytes": algorithmic, "floor_bytes": distinct * d * elem_bytes,
+           "screened": screened, "candidate_rows": valid, "distinct_rows": distinct, "rows_fetched": union_rows if union_rows >= 0 else None}
+    if screened:
+        # per fetched row: the row (padded to 32 elements), its number and its queries (8 B); per query: the query in binary16;
+        # per candidate: the approximate dissimilarity, or its two bounds (Euclidean)
+        ld = (d + 31) // 32 * 32
+        acc["requested_bytes"] = union_rows * (ld * 2 + 8) + nq * ld * 2 + valid * (8 if wl.metric == 1 else 4)
+    elif union_rows >= 0:
         # per fetched row: the row, its number (4 B), query mask (2 B) and output positions (8 x 2 B); per query: the
         # query itself; per candidate: distance (4 B) and id (8 B) written
         acc["requested_bytes"] = union_rows * (d * elem_bytes + 22) + nq * d * 4 + valid * 12
@@ -468,6 +479,8 @@ def main():
     if args.rerank == "f16":
         bound, amount, peak, unit = models["rerank"]
         models["rerank"] = (bound, amount / 2, peak, unit)           # two bytes per gathered element
+    if gather and gather["requested_bytes"]:
+        models["rerank"] = ("hbm", gather["requested_bytes"] * (nq / min(nq, 32768)) / 1e9, PEAK_HBM_GBS, "GB/s")
     kernels = []
     for name, (ms, launches) in prof.items():
         if launches == 0:
@@ -481,7 +494,7 @@ def main():
             if amount is not None:
                 ach = amount / (ms / K / 1e3)
                 ent.update({"achieved": round(ach, 3), "peak": round(peak, 1), "unit": unit, "frac": round(ach / peak, 4)})
-                if name == "rerank":
+                if name == "rerank" and not gather:
                     ent["note"] = "algorithmic bytes (every query gathers its m rows); see roofline for the bytes the kernel requests"
         kernels.append(ent)
     kernels.sort(key=lambda e: -e["avg_ms"])
@@ -498,16 +511,16 @@ def main():
         avg_ms = ms / max(1, launches)
         per_step_ms = ms / K if prof_dom.get("rerank", (0, 0))[1] else avg_ms * dom["launches_per_step"]
         acc = gather or {"algorithmic_bytes": nq * m * wl.d * RERANK_ELEM_BYTES.get(args.rerank, 4), "requested_bytes": None,
-                         "floor_bytes": None, "rows_fetched": None, "distinct_rows": None, "candidate_rows": None}
+                         "floor_bytes": None, "screened": False, "rows_fetched": None, "distinct_rows": None, "candidate_rows": None}
         scale_b = nq / min(nq, 32768)            # the accounting pass covers one launch (at most 32768 queries)
         req = acc["requested_bytes"] * scale_b if acc["requested_bytes"] else None
         alg = nq * m * wl.d * RERANK_ELEM_BYTES.get(args.rerank, 4)
         num = req if req else alg
         rate = num / 1e9 / (per_step_ms / 1e3)
-        traffic = tracked_traffic_gb(args.workload, "k_group_gather") if (args.scale == 1.0 and not args.batch and args.rerank == "f32") else None
+        traffic = tracked_traffic_gb(args.workload, "k_screen_gather" if acc["screened"] else "k_group_gather") if (args.scale == 1.0 and not args.batch and args.rerank == "f32") else None
         roofline = {"kernel": "rerank", "bound": "hbm", "achieved": round(rate, 1), "peak": PEAK_HBM_GBS, "unit": "GB/s",
                     "frac": round(rate / PEAK_HBM_GBS, 4), "avg_ms": round(avg_ms, 5),
-                    "bytes": "requested by the kernel in this run: each candidate row once per group of 8 queries that share it, plus queries, row lists and results" if req else "algorithmic",
+                    "bytes": f"requested by the kernel in this run: each candidate row once, {'as binary16' if acc['screened'] else 'at its stored width'}, per group of {16 if acc['screened'] else 8} queries that share it, plus queries, row lists and results" if req else "algorithmic",
                     "requested_gb": round(num / 1e9, 4), "algorithmic_gb": round(alg / 1e9, 4),
                     "algorithmic_rate": round(alg / 1e9 / (per_step_ms / 1e3), 1),
                     "floor_gb": round(acc["floor_bytes"] * scale_b / 1e9, 4) if acc["floor_bytes"] else None,
