@@ -23,6 +23,9 @@
 // (d/64 + 16) 2^-24 |q| |x|.  All norms are rounded up by 1e-3 relative.
 // With E the bound, A_k the k-th smallest approximate value: k candidates have an exact value <= A_k + E, so everything among
 // the k best (ties included) has an approximate value <= A_k + 2 E.  Values that are not numbers are never dropped.
+// Where a float sum of the exact evaluation may overflow (|q| |x| beyond 1e38, or the |q| a cosine is divided by), values that are far
+// apart tie at an infinity or at one, and the lowest ids win: every candidate of such a query is kept.  (Euclidean: a query of that
+// length has c0 beyond every 2 |q| |x|, the rows of the copy being at most 65504 sqrt(d) long.)
 #pragma once
 #include "common.hpp"
 #include "rerank.hpp"
@@ -201,6 +204,7 @@ __global__ __launch_bounds__(kScreenUnionThreads) void k_screen_union(ScreenRera
                 // in the scaled query's units; cosine: 1 - v / |q| rounds, so values that differ by a few 2^-24 |q| may tie
                 st.x = 1.001f * (qe * a.norm + qh * a.err + acc * qh * (a.norm + a.err) + gam * qn * a.norm +
                                  (a.metric == 2 ? 4.8e-7f * qn * (1.0f + a.norm) : 0.0f)) + s * 1.4e-45f * (float)(a.d + 64) + 1e-30f;
+                if (!(qn * inv * (a.norm + a.err) < 1e38f)) st.x = INFINITY;         // a partial sum of the exact value may overflow
                 st.y = 0.0f; st.z = 0.0f;
             }
             st.w = inv;
@@ -474,7 +478,7 @@ __global__ __launch_bounds__(256) void k_screen_finish(ScreenRerankArgs a) {
     float thr = key_to_float(kth | 255u);
     if (!L2) thr += 2.0f * qs.x;
     thr += 1e-6f * fabsf(thr);
-    if (cosine && !(qn > 1e-15f)) thr = NAN;          // (a zero query ties with everything: nothing is dropped)
+    if (cosine && !(qn > 1e-15f && qn < INFINITY)) thr = NAN;      // (a query of length zero or infinity ties with everything: nothing is dropped)
     if (lane == 0 && w0 == 0) s_cnt[sub] = 0;
     meet_sel();
 #pragma unroll

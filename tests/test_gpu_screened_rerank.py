@@ -97,3 +97,30 @@ def test_few_queries_per_cluster(B, nq):
     np.testing.assert_array_equal(s_ids, e_ids)
     np.testing.assert_array_equal(s_d, e_d)
     gix.close()
+
+
+@pytest.mark.parametrize("half", [False, True])
+@pytest.mark.parametrize("metric,scales", [(0, (3e36, 1e37, 3e37)), (1, (1e18, 2e18, 4e18, 1e20, 1e24)), (2, (2e18, 3e18, 1e20, 1e30))])
+def test_distances_that_overflow_tie_by_id(B, metric, scales, half):
+    """Queries so long that an exact distance - or the norm a cosine is divided by - is infinite in float: the plain re-rank then
+    orders many candidates by their id, and so must the screened one, whose scaled products stay finite."""
+    rng = np.random.default_rng(40 + metric)
+    ix = _random_index(rng, n=4000, d=64, L=6, r=8, metric=metric, dp=32)
+    ix["scale_A"] = (ix["scale_A"] * 1e-6).astype(np.float32)            # (the estimated scores stay finite)
+    q = rng.normal(size=(70, 64)).astype(np.float32)
+    if metric == 0:       # positive elements: sums run into +inf, never into inf - inf
+        ix["corpus"] = (np.abs(ix["corpus"]) * np.exp(rng.normal(size=(4000, 1)))).astype(np.float32)
+        q = np.abs(q)
+    for i, s in enumerate(scales):
+        q[i::len(scales) + 1] *= np.float32(s)
+    gix = B.Index(**ix)
+    if half:
+        gix.set_rerank(B.RERANK_F16)
+    s_ids, s_d = gix.search(q, 10, 4, 100)
+    gix.set_exact_selection(True)
+    e_ids, e_d = gix.search(q, 10, 4, 100)
+    gix.close()
+    np.testing.assert_array_equal(s_d, e_d)
+    np.testing.assert_array_equal(s_ids, e_ids)
+    tied = (e_d[:, 1:] == e_d[:, :-1]).all(axis=1)
+    assert tied.any() and not tied.all()
