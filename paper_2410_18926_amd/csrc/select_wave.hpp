@@ -15,6 +15,7 @@
 #pragma once
 #include "score_mfma.hpp"
 #include "select_query.hpp"
+#include "walk_offsets.hpp"
 
 namespace lorann {
 
@@ -42,7 +43,6 @@ __device__ __forceinline__ int wave_prefix_i32(int v) {
 constexpr int kSelectWaveMaxM = 864;
 inline int select_wave_epl(int m) { return m <= 352 ? 8 : 16; }
 inline size_t select_wave_lds(int epl, int w) { return 4 * ((size_t)epl * 64 * 8 + kWaveBins * 4 + (size_t)((w + 3) & ~3) * 20); }
-constexpr int64_t kSelectWaveMaxCluster = int64_t(1) << 25;      // byte offsets inside a cluster stay below 2^31
 
 // grid = 8 * ceil(ceil(nq / 4) / 8) rounded up to whole runs (see select_query.hpp for the order of the queries), block = 256: four
 // independent wavefronts, dynamic LDS = select_wave_lds bytes.  RB = r_pad / 16; EXT: column-wise step sizes (and, if pt_first is
@@ -179,7 +179,7 @@ __global__ __launch_bounds__(256) void k_select_wave(QuerySelectArgs a) {
         const int m_c = __builtin_amdgcn_readfirstlane(pcnt[jp]), r0 = __builtin_amdgcn_readfirstlane(prow[jp]);
         const float sp = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(psig[jp]))), r0p = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(prho[jp])));
         const i32x4* zp = reinterpret_cast<const i32x4*>(a.Z) + (size_t)__builtin_amdgcn_readfirstlane(ppos[jp]) * RB;
-        // the cluster's codes, norms, ... as buffers: lanes beyond its end read zeros, and no lane computes an address
+        // the cluster's codes, norms, ... as buffers: lanes beyond its end read zeros (walk_offsets.hpp), and no lane computes an address
         const auto codes = __builtin_amdgcn_make_buffer_rsrc(const_cast<int8_t*>(a.Bp) + (size_t)r0 * (RB * 16), 0, m_c * (RB * 16), 0x00027000);
         const auto norms = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(L2 ? a.sqnorm + r0 : reinterpret_cast<const float*>(a.Bp)), 0, L2 ? m_c * 4 : 0, 0x00027000);
         const auto steps = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(EXT ? a.pt_scale + r0 : reinterpret_cast<const float*>(a.Bp)), 0, EXT ? m_c * 4 : 0, 0x00027000);
@@ -189,12 +189,14 @@ __global__ __launch_bounds__(256) void k_select_wave(QuerySelectArgs a) {
         for (int u = 0; u < RB; ++u) zv[u] = zp[u];
         struct Piece { i32x4 code[RB]; float bias, scale, first; };
         auto request = [&](Piece& pc, int own, int base) {       // point base + own: base uniform, own of the lane
+            constexpr int CB = RB * 16;
+            const PieceOffset at = piece_offset(own, base, CB), at4 = piece_offset(own, base, 4);
 #pragma unroll
-            for (int u = 0; u < RB; ++u) pc.code[u] = __builtin_bit_cast(i32x4, __builtin_amdgcn_raw_buffer_load_b128(codes, own * (RB * 16) + 16 * u, base * (RB * 16), 0));
-            if (L2) pc.bias = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(norms, own * 4, base * 4, 0));
+            for (int u = 0; u < RB; ++u) pc.code[u] = __builtin_bit_cast(i32x4, __builtin_amdgcn_raw_buffer_load_b128(codes, at.vector + 16 * u, at.scalar, 0));
+            if (L2) pc.bias = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(norms, at4.vector, at4.scalar, 0));
             if (EXT) {
-                pc.scale = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(steps, own * 4, base * 4, 0));
-                pc.first = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(firsts, own * 4, base * 4, 0));
+                pc.scale = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(steps, at4.vector, at4.scalar, 0));
+                pc.first = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(firsts, at4.vector, at4.scalar, 0));
             }
         };
         // entries that arrived as scores (or integer scores) of this cluster become keys and are counted in the bins
@@ -281,7 +283,7 @@ __global__ __launch_bounds__(256) void k_select_wave(QuerySelectArgs a) {
         if (nq4 == 0) {
             Piece ring[4];
 #pragma unroll
-            for (int b = 0; b < 3; ++b) request(ring[b], lane, 64 * b);
+            for (int b = 0; b < kWalkAhead; ++b) request(ring[b], lane, 64 * b);
 #pragma unroll
             for (int u = 0; u < ZW; ++u) z[u] = __builtin_amdgcn_readfirstlane(zv[u >> 2][u & 3]);
             // (no branch around the requests: the compiler would copy the pieces at the join and wait for them; pieces beyond the end
@@ -289,7 +291,7 @@ __global__ __launch_bounds__(256) void k_select_wave(QuerySelectArgs a) {
             for (int p0 = 0; p0 < m_c && !overflow; p0 += 256) {
 #pragma unroll
                 for (int b = 0; b < 4; ++b) {
-                    request(ring[(b + 3) & 3], lane, p0 + 64 * b + 192);
+                    request(ring[(b + kWalkAhead) & 3], lane, p0 + 64 * (b + kWalkAhead));
                     score(ring[b], lane, p0 + 64 * b);
                 }
             }
@@ -309,7 +311,7 @@ __global__ __launch_bounds__(256) void k_select_wave(QuerySelectArgs a) {
             for (int i0 = 0; i0 < nq4 && !overflow; i0 += 64) {
                 const uint32_t k = sub_key(i0 + lane);
                 unsigned long long todo = __ballot(k != 0u && k >= T);
-                const int own = (lane >> 3) * 32 + (lane & 7);
+                const int own = quarter_point(lane);
                 auto next = [&]() {                      // first point of the next quarter; none left: beyond the cluster's end (uniform)
                     if (todo == 0ull) return m_c;
                     const int i = i0 + __ffsll(todo) - 1;
@@ -319,20 +321,20 @@ __global__ __launch_bounds__(256) void k_select_wave(QuerySelectArgs a) {
                 Piece ring[4];
                 int t0 = next(), t1 = next();
                 request(ring[0], own, t0);
-                request(ring[1], own, t0 + 256);
+                request(ring[1], own, t0 + kQuarterHalf);
                 request(ring[2], own, t1);
-                request(ring[3], own, t1 + 256);
+                request(ring[3], own, t1 + kQuarterHalf);
                 while (t0 < m_c && !overflow) {          // uniform
                     score(ring[0], own, t0);
-                    score(ring[1], own, t0 + 256);
+                    score(ring[1], own, t0 + kQuarterHalf);
                     t0 = next();
                     request(ring[0], own, t0);
-                    request(ring[1], own, t0 + 256);
+                    request(ring[1], own, t0 + kQuarterHalf);
                     score(ring[2], own, t1);
-                    score(ring[3], own, t1 + 256);
+                    score(ring[3], own, t1 + kQuarterHalf);
                     t1 = next();
                     request(ring[2], own, t1);
-                    request(ring[3], own, t1 + 256);
+                    request(ring[3], own, t1 + kQuarterHalf);
                 }
             }
         }
