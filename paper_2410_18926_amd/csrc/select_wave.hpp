@@ -4,7 +4,8 @@
 // scores' distances from the query's best one, the exact top-m selected once at the end - but nothing is shared between
 // wavefronts: the number of held scores is a scalar, there are no barriers, and the memory latency of one query's short
 // clusters is covered by the other queries of the SIMD instead of by its own four wavefronts waiting for each other.
-// The list is shorter (512 or 1024 entries: LDS decides how many queries a CU holds) and is thinned out whenever it fills.
+// The list is shorter (512 or 1024 entries: LDS decides how many queries a CU holds) and is thinned out whenever it fills - down to
+// the m best exactly if need be, ties to the lower rows, so that no number of equal scores overflows it.
 // In a large cluster only the quarters of work items whose best score (kept by the scoring kernel) reaches T are looked at; those
 // best scores, each of another point, first raise T themselves.
 //
@@ -111,7 +112,7 @@ __global__ __launch_bounds__(256) void k_select_wave(QuerySelectArgs a) {
     uint32_t T = 0u;          // running threshold key, at most the m-th best score seen so far (0: none yet)
     float Tf = -INFINITY;     // the same as a score
     int n = 0, n_keys = 0;    // entries in the list, those of them that are keys (uniform)
-    bool overflow = false;
+    uint32_t T_tie = 0u, R_tie = 0u;      // m of the entries seen beat every later one of key T_tie in a row beyond R_tie
     const unsigned long long below = (1ull << lane) - 1ull;
 
     auto read_bins = [&]() {                    // T := far edge of the bin that holds the m-th best score seen (n >= m)
@@ -137,15 +138,17 @@ __global__ __launch_bounds__(256) void k_select_wave(QuerySelectArgs a) {
         return bin;
     };
     auto set_threshold = [&]() { Tf = T > 0x007fffffu ? key_to_float(T) : -INFINITY; };
-    auto thin_out = [&]() {                     // keep the entries >= T (stable, in place)
+    auto thin_out = [&]() {                     // keep the entries >= T, of those equal to T the ones that can still count (stable, in place)
         lds_sync();
+        const uint32_t R = T == T_tie ? R_tie : 0x7fffffffu;
         int kept = 0;
         for (int i0 = 0; i0 < n; i0 += 64) {
             const int i = i0 + lane;
             const uint32_t k = i < n ? keys[i] : 0u;
             const int32_t r = i < n ? rows[i] : 0;
-            const unsigned long long mk = __ballot(i < n && k >= T);
-            if (i < n && k >= T) { const int at = kept + __popcll(mk & below); keys[at] = k; rows[at] = r; }
+            const bool in = i < n && (k > T || (k == T && (uint32_t)r <= R));
+            const unsigned long long mk = __ballot(in);
+            if (in) { const int at = kept + __popcll(mk & below); keys[at] = k; rows[at] = r; }
             kept += __popcll(mk);
             lds_sync();
         }
@@ -167,6 +170,17 @@ __global__ __launch_bounds__(256) void k_select_wave(QuerySelectArgs a) {
         exact = at_lo == m;
         return lo;
     };
+    // Smallest row with at least `need` of the list's entries of key K in rows up to it.
+    auto row_of_ties = [&](uint32_t K, int need) {
+        uint32_t lo = 0u, hi = 0x7fffffffu;
+        while (lo < hi) {                        // uniform
+            const uint32_t mid = lo + ((hi - lo) >> 1);
+            int c = 0;
+            for (int i0 = 0; i0 < n; i0 += 64) c += __popcll(__ballot(i0 + lane < n && keys[i0 + lane] == K && (uint32_t)rows[i0 + lane] <= mid));
+            if (c >= need) hi = mid; else lo = mid + 1u;
+        }
+        return lo;
+    };
     auto load_keys = [&](uint32_t (&ek)[EPL]) {
         lds_sync();
 #pragma unroll
@@ -175,7 +189,7 @@ __global__ __launch_bounds__(256) void k_select_wave(QuerySelectArgs a) {
 
     constexpr bool INT = !L2 && !EXT;           // one scale per pair, no bias: integer scores are compared, and converted once accepted
     int n_read = 0, bin = 0;                    // entries when the bins were last read
-    for (; best != 0u && best >= T && !overflow; jp = next_pair(best)) {       // in falling order: no later cluster can reach T either
+    for (; best != 0u && best >= T; jp = next_pair(best)) {       // in falling order: no later cluster can reach T either
         const int m_c = __builtin_amdgcn_readfirstlane(pcnt[jp]), r0 = __builtin_amdgcn_readfirstlane(prow[jp]);
         const float sp = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(psig[jp]))), r0p = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(prho[jp])));
         const i32x4* zp = reinterpret_cast<const i32x4*>(a.Z) + (size_t)__builtin_amdgcn_readfirstlane(ppos[jp]) * RB;
@@ -225,13 +239,19 @@ __global__ __launch_bounds__(256) void k_select_wave(QuerySelectArgs a) {
             convert();
             bin = read_bins();
             thin_out();
-            if (n > LIMIT) {                             // one bin holds too many: select exactly
+            if (n > LIMIT) {                             // one bin holds too many: the m best (m <= LIMIT - 96), ties to the lower rows
                 uint32_t ek[EPL];
                 load_keys(ek);
                 bool exact;
                 T = mth_largest(ek, max(T, 1u), 0xffffffffu, exact);
+                if (!exact) {
+                    int above = 0;
+#pragma unroll
+                    for (int e = 0; e < EPL; ++e) above += __popcll(__ballot(ek[e] > T));
+                    R_tie = row_of_ties(T, m - above);
+                    T_tie = T;
+                }
                 thin_out();
-                overflow = n > LIMIT;                    // too many scores tie with the threshold
             }
             n_keys = n;
             set_threshold();
@@ -258,7 +278,7 @@ __global__ __launch_bounds__(256) void k_select_wave(QuerySelectArgs a) {
             }
             in = in && base + own < m_c;
             const unsigned long long mk = __ballot(in);
-            if (mk && !overflow) {
+            if (mk) {
                 if (in) {
                     const int at = n + __popcll(mk & below);
                     keys[at] = raw;
@@ -288,7 +308,7 @@ __global__ __launch_bounds__(256) void k_select_wave(QuerySelectArgs a) {
             for (int u = 0; u < ZW; ++u) z[u] = __builtin_amdgcn_readfirstlane(zv[u >> 2][u & 3]);
             // (no branch around the requests: the compiler would copy the pieces at the join and wait for them; pieces beyond the end
             // read zeros and add nothing)
-            for (int p0 = 0; p0 < m_c && !overflow; p0 += 256) {
+            for (int p0 = 0; p0 < m_c; p0 += 256) {
 #pragma unroll
                 for (int b = 0; b < 4; ++b) {
                     request(ring[(b + kWalkAhead) & 3], lane, p0 + 64 * (b + kWalkAhead));
@@ -308,7 +328,7 @@ __global__ __launch_bounds__(256) void k_select_wave(QuerySelectArgs a) {
                 int_threshold();
             }
             // a quarter is two pieces of eight runs of eight points; two quarters are on their way at any time
-            for (int i0 = 0; i0 < nq4 && !overflow; i0 += 64) {
+            for (int i0 = 0; i0 < nq4; i0 += 64) {
                 const uint32_t k = sub_key(i0 + lane);
                 unsigned long long todo = __ballot(k != 0u && k >= T);
                 const int own = quarter_point(lane);
@@ -324,7 +344,7 @@ __global__ __launch_bounds__(256) void k_select_wave(QuerySelectArgs a) {
                 request(ring[1], own, t0 + kQuarterHalf);
                 request(ring[2], own, t1);
                 request(ring[3], own, t1 + kQuarterHalf);
-                while (t0 < m_c && !overflow) {          // uniform
+                while (t0 < m_c) {                       // uniform
                     score(ring[0], own, t0);
                     score(ring[1], own, t0 + kQuarterHalf);
                     t0 = next();
@@ -338,19 +358,11 @@ __global__ __launch_bounds__(256) void k_select_wave(QuerySelectArgs a) {
                 }
             }
         }
-        if (overflow) break;
         convert();
         if (n >= m && n != n_read) { bin = read_bins(); set_threshold(); n_read = n; }
     }
 
     int32_t* out = a.cand + (size_t)q * m;
-    if (overflow) {
-        if (lane == 0) {
-            a.fb_list[atomicAdd(a.fb_count, 1)] = q; a.n_kept[q] = -1; a.tau[q] = key_to_float(T);
-            a.qkey[q] = prow[jp];                        // (a locality hint only)
-        }
-        return;
-    }
     uint32_t ek[EPL];
     load_keys(ek);
     uint32_t K = 0u, lowest = 0xffffffffu;
@@ -361,26 +373,16 @@ __global__ __launch_bounds__(256) void k_select_wave(QuerySelectArgs a) {
         K = mth_largest(ek, max(T, 1u), max(hi, T + 1u), exact);
     }
     // entries above K, and of those equal to it the ones in the lowest rows
-    int need = 0;
     uint32_t R = 0xffffffffu;
-    int32_t er[EPL];
-#pragma unroll
-    for (int e = 0; e < EPL; ++e) er[e] = 64 * e + lane < n ? rows[64 * e + lane] : 0x7fffffff;
     if (!exact) {
         int above = 0;
 #pragma unroll
         for (int e = 0; e < EPL; ++e) above += __popcll(__ballot(ek[e] > K));
-        need = m - above;                                // 1 <= need < the entries equal to K
-        uint32_t lo = 0u, hi = 0x7fffffffu;              // smallest R with at least `need` of them in rows <= R
-        while (lo < hi) {                                // uniform
-            const uint32_t mid = lo + ((hi - lo) >> 1);
-            int c = 0;
-#pragma unroll
-            for (int e = 0; e < EPL; ++e) c += __popcll(__ballot(ek[e] == K && (uint32_t)er[e] <= mid));
-            if (c >= need) hi = mid; else lo = mid + 1u;
-        }
-        R = lo;
+        R = row_of_ties(K, m - above);                   // 1 <= m - above < the entries equal to K
     }
+    int32_t er[EPL];
+#pragma unroll
+    for (int e = 0; e < EPL; ++e) er[e] = 64 * e + lane < n ? rows[64 * e + lane] : 0x7fffffff;
     int at0 = 0, mn = 0x7fffffff;
 #pragma unroll
     for (int e = 0; e < EPL; ++e) {

@@ -71,3 +71,28 @@ def test_one_cluster_holds_most_points(B, metric, r, m, nq, scheme):
     np.testing.assert_array_equal(np.sort(st["cand_rows"].astype(np.int64), axis=1), np.sort(ost["cand_rows"], axis=1))
     np.testing.assert_array_equal(st["pmax"], ost["pair_best"])
     gix.close()
+
+
+@pytest.mark.parametrize("metric,m,scheme", [(0, 10, "cluster"), (0, 352, "cluster"), (2, 353, "cluster"), (0, 864, "cluster"), (1, 352, "cluster"), (1, 700, "mixed"), (0, 300, "columns")])
+def test_more_ties_than_the_list_holds(B, metric, m, scheme):
+    """Thousands of points share the m-th score of nearly every query, a few hundred score higher: the list is cut back to the m best
+    (ties to the lower rows) as often as it fills, and no query is handed to the exhaustive kernel."""
+    ix = _index(metric, n=24_000, L=6, r=16, seed=5)
+    ix.cluster_offsets[:] = torch.tensor([0, 9000, 9000, 13_000, 13_500, 17_600, 24_000])
+    ix.B[:] = 1
+    ix.B[7::90] = 100                                     # (a score is this code times the sum of the query's)
+    ix.corpus[:] = ix.corpus / ix.corpus.norm(dim=1, keepdim=True)
+    if metric == 1:
+        ix.corpus[:] = ix.corpus[0]                       # equal norms to the last bit
+    if scheme != "cluster":
+        ix.scale_A_columns, ix.scale_B_points = torch.full((6, 16), 1e-3), torch.full((24_000,), 1.25)
+    if scheme == "mixed":
+        ix.first_row_A, ix.first_row_B = torch.full((6, 16), 0.5), torch.ones(24_000)
+    queries = np.random.default_rng(m).standard_normal((2100, 32)).astype(np.float32)
+    gix = B.Index.from_arrays(ix.to("cuda"))
+    _, _, st = gix.search_stages(torch.from_numpy(queries).cuda(), 5, 4, m)
+    gix.close()
+    some = np.arange(0, 2100, 20)
+    _, _, ost = O.search(O.OracleIndex(ix.numpy()), queries[some], 5, 4, m, stages=True)
+    np.testing.assert_array_equal(np.sort(st["cand_rows"][some].astype(np.int64), axis=1), np.sort(ost["cand_rows"], axis=1))
+    assert (st["n_survivors"] >= 0).all()
