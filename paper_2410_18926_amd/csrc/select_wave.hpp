@@ -220,7 +220,7 @@ __global__ __launch_bounds__(256) void k_select_wave(QuerySelectArgs a) {
                 const int i = i0 + lane;
                 if (i < n) {
                     const float sc = INT ? __fmaf_rn((float)(int)keys[i], sp, -0.0f) : __uint_as_float(keys[i]);
-                    const uint32_t key = float_key_asc(sc);
+                    const uint32_t key = min(float_key_asc(sc), 0xfffffffeu);      // (a NaN of all ones: mth_largest needs a key above all)
                     keys[i] = key;
                     atomicAdd(&bins[wave_bin(key < kmax ? kmax - key : 0u)], 1);
                 }

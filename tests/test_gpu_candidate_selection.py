@@ -96,3 +96,17 @@ def test_more_ties_than_the_list_holds(B, metric, m, scheme):
     _, _, ost = O.search(O.OracleIndex(ix.numpy()), queries[some], 5, 4, m, stages=True)
     np.testing.assert_array_equal(np.sort(st["cand_rows"][some].astype(np.int64), axis=1), np.sort(ost["cand_rows"], axis=1))
     assert (st["n_survivors"] >= 0).all()
+
+
+@pytest.mark.parametrize("m", [10, 400])
+def test_scores_that_are_no_numbers(B, m):
+    """Norms that are NaN with every bit set give scores with the largest key there is: each query still gets exactly m distinct rows."""
+    ix = _index(1, n=12_000, L=6, r=16, seed=8)
+    ix.cluster_offsets[:] = torch.tensor([0, 3000, 6000, 8000, 9000, 10_000, 12_000])
+    ix.corpus[::5, 0] = torch.tensor([-1], dtype=torch.int32).view(torch.float32)
+    queries = np.random.default_rng(m).standard_normal((2100, 32)).astype(np.float32)
+    gix = B.Index.from_arrays(ix.to("cuda"))
+    _, _, st = gix.search_stages(torch.from_numpy(queries).cuda(), 5, 6, m)
+    gix.close()
+    rows = np.sort(st["cand_rows"], axis=1)
+    assert rows.min() >= 0 and rows.max() < 12_000 and (rows[:, 1:] > rows[:, :-1]).all()
