@@ -267,7 +267,7 @@ __global__ __launch_bounds__(64 * WPB) void k_pair_max(ScoreArgs a) {
 #pragma unroll
                     for (int jj = 8 * s; jj < 8 * s + 8; ++jj) rs = max(rs, (unsigned)col[jj * TRS]);
                     r = max(r, rs);
-                    quarter[s] = rs == float_key_asc(-INFINITY) ? 0u : rs;
+                    quarter[s] = rs;      // (no point and points of score -inf look alike: the walk looks into both, and finds nothing in the first)
                 }
                 s_red[wv][p] = (int)r;
             }

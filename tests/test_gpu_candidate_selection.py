@@ -110,3 +110,22 @@ def test_scores_that_are_no_numbers(B, m):
     gix.close()
     rows = np.sort(st["cand_rows"], axis=1)
     assert rows.min() >= 0 and rows.max() < 12_000 and (rows[:, 1:] > rows[:, :-1]).all()
+
+
+@pytest.mark.parametrize("m", [250, 700])
+def test_points_of_infinite_norm_fill_up_the_candidates(B, m):
+    """Squared Euclidean, most points of a large cluster with a norm beyond the float range (score -inf): with fewer finite scores than
+    candidates asked for, the lowest rows of the others follow, also where the walk goes by the best scores of quarters."""
+    ix = _index(1, n=43_000, L=2, r=16, seed=13)
+    ix.cluster_offsets[:] = torch.tensor([0, 41_111, 43_000])
+    far = torch.ones(43_000, dtype=torch.bool)
+    far[130::137] = False                                 # 300 of the large cluster, 13 of the other
+    ix.corpus[far] *= 1e20
+    queries = np.random.default_rng(m).standard_normal((2100, 32)).astype(np.float32)
+    gix = B.Index.from_arrays(ix.to("cuda"))
+    q = torch.from_numpy(queries).cuda()
+    _, _, st = gix.search_stages(q, 5, 1, m)
+    gix.set_exact_selection(True)
+    _, _, e_st = gix.search_stages(q, 5, 1, m)
+    gix.close()
+    np.testing.assert_array_equal(np.sort(st["cand_rows"], axis=1), np.sort(e_st["cand_rows"], axis=1))
