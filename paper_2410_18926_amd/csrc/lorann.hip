@@ -157,6 +157,8 @@ struct lorann_index {
     int32_t metric = 0, d = 0, dp = 0, r = 0, r_pad = 0, L = 0;
     int64_t n = 0;
     int64_t max_cluster = 0;        // points of the largest cluster
+    int32_t* sub_first = nullptr;   // [L] places of the quarter maxima (quarters.hpp; NULL: no cluster has any)
+    QuarterLayout quarters;
     hipStream_t stream = nullptr;
     // index data (device)
     float* centroids = nullptr;     // [L][dp]
@@ -207,7 +209,7 @@ struct lorann_index {
 namespace {
 
 void free_all(lorann_index* ix) {
-    void* ptrs[] = {ix->centroids, ix->cent_sqnorm, ix->cent_nrm_f32, ix->cent_bf16, ix->Pt, ix->A, ix->Bp, ix->sA, ix->sB, ix->sA_cols, ix->sB_pts, ix->A_first, ix->B_first, ix->off, ix->corpus, ix->corpus_h, ix->ids, ix->sqnorm};
+    void* ptrs[] = {ix->centroids, ix->cent_sqnorm, ix->cent_nrm_f32, ix->cent_bf16, ix->Pt, ix->A, ix->Bp, ix->sA, ix->sB, ix->sA_cols, ix->sB_pts, ix->A_first, ix->B_first, ix->off, ix->sub_first, ix->corpus, ix->corpus_h, ix->ids, ix->sqnorm};
     for (void* p : ptrs) if (p) (void)hipFree(p);
     for (Workspace& w : ix->ws) w.release();
     DevBuf* bufs[] = {&ix->stage_q, &ix->stage_ids, &ix->stage_dists, &ix->fb_total};
@@ -310,7 +312,6 @@ int prof_settle(lorann_index* ix) {
 
 int next_pow2(int v) { int p = 1; while (p < v) p <<= 1; return p; }
 
-constexpr int kSubMaxItems = 192 * 1024; // quarter maxima of at most this many scoring work items are kept (1 KiB each)
 constexpr int kSmallPathQueries = 64;   // batches up to this size take the query-major path
 constexpr int kNZ = 2;                 // 32-pair tiles per scoring unit
 constexpr int kUnitPairs = 32 * kNZ;
@@ -318,12 +319,13 @@ constexpr int kChunkTiles = 16;       // 32-point tiles per scoring work item
 constexpr int ilog2_exact(int v) { return v == 1 ? 0 : 1 + ilog2_exact(v / 2); }
 constexpr int kUnitShift = ilog2_exact(kUnitPairs), kChunkShift = ilog2_exact(32 * kChunkTiles);
 static_assert((1 << kUnitShift) == kUnitPairs && (1 << kChunkShift) == 32 * kChunkTiles, "work items are powers of two");
+static_assert(kUnitPairs == kGroupPairs && 32 * kChunkTiles == kChunkPoints, "the layout of the quarter maxima follows the work items");
 // which shape the pair-maxima kernel takes: at most 16 pairs per cluster on average -> one wavefront streams a cluster
 inline bool pair_max_streams(int64_t npairs, int L) { return npairs <= (int64_t)16 * L; }
 
 // S7 on the int8 matrix cores: the best score of every (query, cluster) pair.  With y_off / y (verification) the
 // instantiation that also stores every accumulator is launched instead.
-void launch_pair_max(lorann_index* ix, Workspace& ws, hipStream_t s, int64_t npairs, const int64_t* y_off, int32_t* y, bool small = false, int sub_cap = 0) {
+void launch_pair_max(lorann_index* ix, Workspace& ws, hipStream_t s, int64_t npairs, const int64_t* y_off, int32_t* y, bool small = false, int sub_chunks = 0, int sub_groups = 0) {
     const int L = small ? (int)npairs : ix->L;       // small batches: every pair is a cluster of its own
     const bool l2 = ix->metric == LORANN_L2, mixed = ix->A_first != nullptr;
     const int ks = ix->r_pad / 32;
@@ -333,7 +335,7 @@ void launch_pair_max(lorann_index* ix, Workspace& ws, hipStream_t s, int64_t npa
     sc.sqnorm = l2 ? ix->sqnorm : nullptr; sc.pt_scale = ix->sB_pts; sc.pt_first = ix->B_first; sc.rho0 = mixed ? ws.rho0.as<float>() : nullptr; sc.pmax = ws.pmax.as<uint32_t>(); sc.L = L; sc.chunk_tiles = kChunkTiles;
     sc.slot_of_pos = ws.slot_of_pos.as<int32_t>(); sc.y_off = y_off; sc.y = y;
     sc.voff = small ? ws.voff.as<int64_t>() : nullptr;
-    sc.sub = sub_cap > 0 ? ws.submax.as<uint32_t>() : nullptr; sc.sub_cap = sub_cap;
+    sc.sub = sub_chunks > 0 ? ws.submax.as<uint32_t>() : nullptr; sc.sub_first = ix->sub_first; sc.sub_chunks = sub_chunks; sc.sub_groups = sub_groups;
     // few pairs per cluster: the kernel streams the codes of the touched clusters, one wavefront per cluster
     const bool stream = small || pair_max_streams(npairs, L);
     const dim3 gs((unsigned)((L + 3) / 4)), gp(2048);   // persistent shape: 8192 wavefronts stride over the work items
@@ -362,7 +364,8 @@ struct ChunkPlan {
     bool handful;       // up to 8 queries: distances and top-k of the re-rank in one launch
     bool screened;      // re-rank screened by the binary16 copy of the corpus
     bool wave_walk;     // candidate selection by one wavefront per query
-    int sub_cap;        // scoring work items whose quarter maxima are kept (large clusters; 0: none)
+    int sub_chunks;     // 512-point chunks of large clusters whose quarter maxima are kept (quarters.hpp; 0: none) ...
+    int sub_groups;     // ... for this many groups of 64 pairs each
     int screen_gq;      // queries per group of the screened re-rank
     int screen_stride;  // list entries per group
     bool small;         // query-major path of small batches (no bucketing)
@@ -401,14 +404,14 @@ ChunkPlan plan_chunk(const lorann_index* ix, int64_t nq, int k, int w, int m, bo
     // Candidate selection: one wavefront per query where many queries share the machine and its short list suffices (microseconds,
     // four wavefronts per query / one: 10 000 queries of the 768-d workload 104 / 74, 2531 queries with m = 777 209 / 140, 10M points
     // 960 / 498 per 100 000 queries; 1000 queries 15 / 19, 1024 queries at 10M points 23 / 27).  A large
-    // cluster would keep such a wavefront busy on its own, so its quarter maxima have to be there (work items only, and not in the
-    // fixed region, which they would fill), else four wavefronts share it.
+    // cluster would keep such a wavefront busy on its own, so the quarter maxima of EVERY cluster beyond kWaveWholePoints have to be
+    // there (work items only, and not in the fixed region, which they would fill), else four wavefronts share each query.
     const bool items = nq > 2048 && !pair_max_streams(nq * w, L);
-    const int64_t max_items = ((int64_t)nq * w / kUnitPairs + L) * (((ix->max_cluster - 1) >> kChunkShift) + 1);     // at most
-    pl.sub_cap = items && !fixed && ix->max_cluster > kSubMinPoints ? (int)std::min<int64_t>(max_items, kSubMaxItems) : 0;
+    pl.sub_groups = (int)quarter_groups(nq);
+    pl.sub_chunks = items && !fixed ? (int)quarter_chunks(ix->quarters.chunks, nq) : 0;
     pl.wave_walk = nq > 2048 && !ix->force_exact && m <= kSelectWaveMaxM && select_wave_lds(select_wave_epl(m), w) <= 64 * 1024 && ix->max_cluster <= kSelectWaveMaxCluster &&
-                   (ix->max_cluster <= 4 * kSubMinPoints || pl.sub_cap > 0);
-    if (!pl.wave_walk) pl.sub_cap = 0;
+                   quarters_suffice(ix->quarters, pl.sub_chunks);
+    if (!pl.wave_walk) pl.sub_chunks = 0;
     pl.handful = pl.small && pl.grouped && nq <= 8 && ix->d % 4 == 0 && ix->d <= 1024 && k <= 64;
     // The screened re-rank reads all candidates at half width and about k of them in full: it pays while k is a small part of m
     // (a row read at half width is shared by about two queries, one read in full is not, so up to k = m / 4).  A few dozen queries are
@@ -459,7 +462,7 @@ int reserve_workspace(const lorann_index* ix, Workspace& ws, const ChunkPlan& pl
         {&ws.rdist, sgroups * (ix->metric == LORANN_L2 ? 8 : 4), pl.screened},
         {&ws.rdist, q * m * 4, pl.grouped || no_rerank}, {&ws.rcid, q * m * 8, pl.grouped || no_rerank},
         {&ws.rccount, q * 4, pl.grouped || no_rerank || pl.small},      // (small batches: also the tickets of the one-launch re-rank)
-        {&ws.submax, (size_t)pl.sub_cap * kUnitPairs * 16, pl.sub_cap > 0},
+        {&ws.submax, (size_t)pl.sub_chunks * pl.sub_groups * kUnitPairs * 16, pl.sub_chunks > 0},
         {&ws.smin, q * kFusedSubsets * 4, pl.digest}, {&ws.thr, q * 4, pl.digest},
         {&ws.hit_val, q * kFusedLists * kFusedCap * 64, pl.digest}, {&ws.hit_grp, q * kFusedLists * kFusedCap * 4, pl.digest},
         {&ws.hit_cnt, q * kFusedLists * 4, pl.digest},
@@ -760,7 +763,7 @@ int search_chunk(lorann_index* ix, Workspace& ws, hipStream_t s, const float* dQ
         const int ks = r_pad / 32;
         {
             Prof p(ix, K_PAIR_MAX, s);
-            launch_pair_max(ix, ws, s, npairs, nullptr, nullptr, pl.small, pl.sub_cap);
+            launch_pair_max(ix, ws, s, npairs, nullptr, nullptr, pl.small, pl.sub_chunks, pl.sub_groups);
         }
         {
             Prof p(ix, K_SELECT_QUERY, s);
@@ -778,7 +781,7 @@ int search_chunk(lorann_index* ix, Workspace& ws, hipStream_t s, const float* dQ
                                         else hipLaunchKernelGGL((k_select_query<RB_, L2_, EXT_, false>), qgrid, dim3(256), qlds, s, qa); } while (0)
 #define LAUNCH_SQ2(RB_, L2_) do { if (ext) LAUNCH_SQ3(RB_, L2_, true); else LAUNCH_SQ3(RB_, L2_, false); } while (0)
 #define LAUNCH_SQ(RB_) do { if (l2) LAUNCH_SQ2(RB_, true); else LAUNCH_SQ2(RB_, false); } while (0)
-            qa.sub = pl.sub_cap > 0 ? ws.submax.as<uint32_t>() : nullptr; qa.bucket_off = ws.bucket_off.as<int32_t>(); qa.unit_off = ws.unit_off.as<int32_t>(); qa.sub_cap = pl.sub_cap;
+            qa.sub = pl.sub_chunks > 0 ? ws.submax.as<uint32_t>() : nullptr; qa.bucket_off = ws.bucket_off.as<int32_t>(); qa.sub_first = ix->sub_first; qa.sub_chunks = pl.sub_chunks; qa.sub_groups = pl.sub_groups;
             if (pl.wave_walk) {
                 const int epl = select_wave_epl(m);
                 const size_t wlds = select_wave_lds(epl, w);
@@ -1203,6 +1206,10 @@ int lorann_load_index(lorann_index** out, int32_t metric, int64_t n, int32_t d, 
         if ((e = dev_copy(&ix->sA, scale_A, (size_t)L))) return e;
         if ((e = dev_copy(&ix->sB, scale_B, (size_t)L))) return e;
         if ((e = dev_copy(&ix->off, off.data(), (size_t)L + 1))) return e;
+        if (ix->max_cluster > kSubMinPoints) {
+            ix->quarters = lay_out_quarters(off.data(), L);
+            if ((e = dev_copy(&ix->sub_first, ix->quarters.first.data(), (size_t)L))) return e;
+        }
         if ((e = dev_copy(&ix->corpus, corpus, (size_t)n * d))) return e;
         if (ids && (e = dev_copy(&ix->ids, ids, (size_t)n))) return e;
         {   // codes padded to r_pad bytes per point so that every point is one or two aligned 32-byte operands

@@ -15,6 +15,7 @@
 // maximum reaches its running m-th best score; every other pair is dismissed by its maximum alone.
 #pragma once
 #include "common.hpp"
+#include "quarters.hpp"
 #include "stage_a.hpp"
 
 namespace lorann {
@@ -36,18 +37,17 @@ struct ScoreArgs {
     int L;
     int chunk_tiles;             // 32-point tiles per work item
     // clusters of more than kSubMinPoints points (items only): also the best score of every quarter of an item's points - those
-    // whose place in their 32-point tile is 8 s .. 8 s + 7 - as keys, [items][pairs of an item][4], so that the candidate selection
-    // can dismiss most of a large cluster; items from sub_cap on have none
+    // whose place in their 32-point tile is 8 s .. 8 s + 7 - as keys, [places][pairs of an item][4] (places: quarters.hpp), so that the
+    // candidate selection can dismiss most of a large cluster; NULL: none
     uint32_t* sub;
-    int sub_cap;
+    const int32_t* sub_first;    // [L]
+    int sub_chunks, sub_groups;
     // verification only (DUMP instantiations): every int32 accumulator of the matrix-core product is written to
     // y[y_off[slot_of_pos[pair]] + point]
     const int32_t* slot_of_pos;  // [npairs] bucket position -> slot (query * w + rank)
     const int64_t* y_off;        // [npairs + 1] offsets of the slots into y
     int32_t* y;
 };
-
-constexpr int kSubMinPoints = 2048;
 
 // Row (within the 32-row tile) of result register v for lane half h.
 __device__ __forceinline__ int tile_row(int v, int h) { return 8 * (v >> 2) + 4 * h + (v & 3); }
@@ -312,9 +312,14 @@ __global__ __launch_bounds__(64 * WPB) void k_pair_max(ScoreArgs a) {
             // consecutive items (the wavefronts of one block) share the point chunk and differ in the pair group,
             // so the chunk's codes are fetched from L2 once per block
             const int pk = local / n_groups, ug = local - pk * n_groups;
+            int sub_at = -1;
+            if (a.sub != nullptr && m_all > kSubMinPoints) {
+                sub_at = a.sub_first[c];
+                if (sub_at + (m_all + kChunkPoints - 1) / kChunkPoints > a.sub_chunks) sub_at = -1;
+            }
             process(pbeg + ug * NP, pend, row_c + (int64_t)pk * 32 * a.chunk_tiles,
                     min(32 * a.chunk_tiles, m_all - pk * 32 * a.chunk_tiles), pk * 32 * a.chunk_tiles,
-                    m_all > kSubMinPoints && item < a.sub_cap ? a.sub + (size_t)item * (4 * NP) : nullptr);
+                    sub_at >= 0 ? a.sub + ((size_t)(sub_at + pk) * a.sub_groups + ug) * (4 * NP) : nullptr);
         }
     }
 }

@@ -108,11 +108,11 @@ struct QuerySelectArgs {
     int nq, w, m;
     int cap;                     // select_query_cap(m)
     int run_shift;               // log2 of the queries per run (see the kernel)
-    // large clusters (score_mfma.hpp), one-wavefront kernel only: best scores of the quarters of every work item, or NULL
-    const uint32_t* sub;         // [items][64][4]
+    // large clusters (quarters.hpp), one-wavefront kernel only: best scores of the quarters of their work items, or NULL
+    const uint32_t* sub;         // [places][64][4]
     const int32_t* bucket_off;   // [L+1]
-    const int32_t* unit_off;     // [L+1]
-    int sub_cap;                 // items that have them
+    const int32_t* sub_first;    // [L]
+    int sub_chunks, sub_groups;
 };
 
 // Dynamic LDS of k_select_query: the list and what is known of each pair.

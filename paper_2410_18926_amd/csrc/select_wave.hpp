@@ -292,12 +292,11 @@ __global__ __launch_bounds__(256) void k_select_wave(QuerySelectArgs a) {
         size_t sub_step = 0;
         if (a.sub && m_c > kSubMinPoints) {              // uniform
             const int c = __builtin_amdgcn_readfirstlane(a.sel[(size_t)q * w + jp]), pos = __builtin_amdgcn_readfirstlane(ppos[jp]);
-            const int pbeg = a.bucket_off[c], groups = (a.bucket_off[c + 1] - pbeg + 63) >> 6, at = pos - pbeg, first = a.unit_off[c];
-            const int chunks = (m_c + 511) >> 9;
-            if (first + groups * chunks <= a.sub_cap) {
+            const int at = pos - a.bucket_off[c], first = a.sub_first[c], chunks = (m_c + kChunkPoints - 1) / kChunkPoints;
+            if (first + chunks <= a.sub_chunks) {
                 nq4 = 4 * chunks;
-                subp = a.sub + ((size_t)first + (at >> 6)) * 256 + (at & 63) * 4;
-                sub_step = (size_t)groups * 256;
+                subp = a.sub + ((size_t)first * a.sub_groups + (at >> 6)) * 256 + (at & 63) * 4;
+                sub_step = (size_t)a.sub_groups * 256;
             }
         }
         if (nq4 == 0) {
