@@ -79,6 +79,7 @@ struct Arena {
 struct DevBuf {
     void* p = nullptr;
     size_t cap = 0;
+    static size_t grown(size_t bytes) { return bytes + bytes / 8 + 256; }
     int reserve(size_t bytes, Arena* arena = nullptr) {
         if (arena) {
             const size_t at = (arena->used + 255) & ~(size_t)255;
@@ -89,7 +90,7 @@ struct DevBuf {
         }
         if (bytes <= cap) return LORANN_OK;
         if (p) { (void)hipFree(p); p = nullptr; cap = 0; }
-        size_t want = bytes + bytes / 8 + 256;
+        const size_t want = grown(bytes);
         hipError_t e = hipMalloc(&p, want);
         if (e != hipSuccess) { (void)hipGetLastError(); p = nullptr; return fail(LORANN_E_NOMEM, "hipMalloc of %zu bytes failed: %s", want, hipGetErrorString(e)); }
         cap = want;
@@ -375,7 +376,7 @@ struct ChunkPlan {
     int64_t ngroups;
 };
 
-ChunkPlan plan_chunk(const lorann_index* ix, int64_t nq, int k, int w, int m, bool fixed = false, bool allow_screened = true) {
+ChunkPlan plan_chunk(const lorann_index* ix, int64_t nq, int k, int w, int m, bool allow_quarters = true, bool allow_screened = true) {
     ChunkPlan pl;
     const int L = ix->L;
     pl.mixed = ix->A_first != nullptr;      // Sec. 4.2: first component of q' and of every r stay in float
@@ -408,7 +409,7 @@ ChunkPlan plan_chunk(const lorann_index* ix, int64_t nq, int k, int w, int m, bo
     // there (work items only, and not in the fixed region, which they would fill), else four wavefronts share each query.
     const bool items = nq > 2048 && !pair_max_streams(nq * w, L);
     pl.sub_groups = (int)quarter_groups(nq);
-    pl.sub_chunks = items && !fixed ? (int)quarter_chunks(ix->quarters.chunks, nq) : 0;
+    pl.sub_chunks = items && allow_quarters ? (int)quarter_chunks(ix->quarters.chunks, nq) : 0;
     pl.wave_walk = nq > 2048 && !ix->force_exact && m <= kSelectWaveMaxM && select_wave_lds(select_wave_epl(m), w) <= 64 * 1024 && ix->max_cluster <= kSelectWaveMaxCluster &&
                    quarters_suffice(ix->quarters, pl.sub_chunks);
     if (!pl.wave_walk) pl.sub_chunks = 0;
@@ -434,8 +435,10 @@ ChunkPlan plan_chunk(const lorann_index* ix, int64_t nq, int k, int w, int m, bo
 }
 
 // Every device buffer of one batch.  All of them are reserved here, before the first launch, so that a workspace
-// that cannot hold the batch is refused while nothing has been enqueued yet.
-int reserve_workspace(const lorann_index* ix, Workspace& ws, const ChunkPlan& pl, int64_t nq, int w, int m) {
+// that cannot hold the batch is refused while nothing has been enqueued yet.  last = false: the caller has a plan that needs less, so
+// what would not fit into the free memory is not even tried (and nothing is given up for it); last = true: buffers that this plan does not
+// use make room if they have to.
+int reserve_workspace(const lorann_index* ix, Workspace& ws, const ChunkPlan& pl, int64_t nq, int w, int m, bool last) {
     const int L = ix->L, dp = ix->dp, r_pad = ix->r_pad;
     const size_t npairs = (size_t)nq * w, q = (size_t)nq;
     Arena* ar = ws.arena;
@@ -467,10 +470,23 @@ int reserve_workspace(const lorann_index* ix, Workspace& ws, const ChunkPlan& pl
         {&ws.hit_val, q * kFusedLists * kFusedCap * 64, pl.digest}, {&ws.hit_grp, q * kFusedLists * kFusedCap * 4, pl.digest},
         {&ws.hit_cnt, q * kFusedLists * 4, pl.digest},
     };
-    bool fits = true;
+    if (!ar && !last) {
+        size_t growth = 0, free_b = 0, total_b = 0;
+        for (const Want& wt : wants) if (wt.on && wt.bytes > wt.b->cap) growth += DevBuf::grown(wt.bytes) - wt.b->cap;
+        if (growth > 0 && hipMemGetInfo(&free_b, &total_b) == hipSuccess && growth > free_b)
+            return fail(LORANN_E_NOMEM, "this search needs %zu more bytes of workspace, %zu are free", growth, free_b);
+    }
+    bool fits = true, room_made = !last;
     for (const Want& wt : wants) {
         if (!wt.on) continue;
-        const int rc = wt.b->reserve(wt.bytes, ar);
+        int rc = wt.b->reserve(wt.bytes, ar);
+        if (rc == LORANN_E_NOMEM && !room_made) {
+            DevBuf* lists[] = {&ws.u_row, &ws.u_mask, &ws.u_pos, &ws.u_count, &ws.u_meta, &ws.qhalf, &ws.qstat, &ws.rdist, &ws.rcid, &ws.rccount, &ws.submax};
+            for (DevBuf* b : lists)
+                if (std::none_of(std::begin(wants), std::end(wants), [&](const Want& o) { return o.on && o.b == b; })) b->release();
+            room_made = true;
+            rc = wt.b->reserve(wt.bytes, ar);
+        }
         if (rc == LORANN_OK) continue;
         if (!ar) return rc;
         fits = false;           // keep adding up: the message states the whole requirement
@@ -481,15 +497,19 @@ int reserve_workspace(const lorann_index* ix, Workspace& ws, const ChunkPlan& pl
     return LORANN_OK;
 }
 
-// The plan of a batch and its buffers.  A search that fits the fixed region only without the screened re-rank's lists goes without.
+// The plan of a batch and its buffers.  Quarter maxima and the lists of the screened re-rank only save time: a search that fits the fixed
+// region, or the memory that is free, only without them goes without (quarter maxima first; the fixed region never holds them).
 int plan_and_reserve(const lorann_index* ix, Workspace& ws, int64_t nq, int k, int w, int m, ChunkPlan& pl) {
-    pl = plan_chunk(ix, nq, k, w, m, ws.arena != nullptr);
-    int rc = reserve_workspace(ix, ws, pl, nq, w, m);
-    if (rc == LORANN_E_UNSUPPORTED && ws.arena && pl.screened) {
-        pl = plan_chunk(ix, nq, k, w, m, true, false);
-        rc = reserve_workspace(ix, ws, pl, nq, w, m);
+    bool quarters = ws.arena == nullptr, screened = true;
+    const std::string said = g_err;
+    for (;;) {
+        pl = plan_chunk(ix, nq, k, w, m, quarters, screened);
+        const bool last = !pl.screened && pl.sub_chunks == 0;
+        const int rc = reserve_workspace(ix, ws, pl, nq, w, m, last);
+        if (last || rc != (ws.arena ? LORANN_E_UNSUPPORTED : LORANN_E_NOMEM)) return rc;
+        g_err = said;         // (a plan that was tried is no failure of the call)
+        if (pl.sub_chunks > 0) quarters = false; else screened = false;
     }
-    return rc;
 }
 
 // The screened re-rank of one batch: union, matrix-core gather over the binary16 rows, exact finish.

@@ -124,3 +124,34 @@ def test_distances_that_overflow_tie_by_id(B, metric, scales, half):
     np.testing.assert_array_equal(s_ids, e_ids)
     tied = (e_d[:, 1:] == e_d[:, :-1]).all(axis=1)
     assert tied.any() and not tied.all()
+
+
+@pytest.mark.parametrize("metric,nq,m,w", [(0, 32768, 4096, 6), (1, 16384, 2000, 4)])
+def test_search_without_room_for_the_screening_lists(B, metric, nq, m, w):
+    """Little free memory: the lists of the screened re-rank (and the quarter maxima) do not fit beside what every search needs.  The search then
+    goes without them, on this call and on later ones, with the same results."""
+    rng = np.random.default_rng(m)
+    ix = _random_index(rng, n=24_000, d=32, L=6, r=8, metric=metric)
+    q = torch.from_numpy(rng.normal(size=(nq, 32)).astype(np.float32)).cuda()
+    ref = B.Index(**ix)
+    r_ids, r_d = ref.search(q, 10, w, m)
+    ref.close()
+    gix = B.Index(**ix)
+    outs = [(torch.empty(nq, 10, dtype=torch.int64, device="cuda"), torch.empty(nq, 10, device="cuda")) for _ in range(3)]
+    torch.cuda.empty_cache()
+    needed = int(1.3 * (nq * (m * 4 + 500) + (32 << 20)))        # candidates and the small buffers, with the workspace's slack of 1/8
+    free = torch.cuda.mem_get_info()[0]
+    assert free > needed
+    hog = torch.empty(free - needed, dtype=torch.uint8, device="cuda")
+    try:
+        gix.search(q, 10, w, m, out=outs[0])
+        gix.search(q, 10, w, m, out=outs[1], asynchronous=True)
+        gix.search(q[:500], 10, w, m, out=(outs[2][0][:500], outs[2][1][:500]))       # small enough for the lists
+        torch.cuda.synchronize()
+    finally:
+        del hog
+        torch.cuda.empty_cache()
+    for ids, d in outs[:2]:
+        assert torch.equal(ids, r_ids) and torch.equal(d, r_d)
+    assert torch.equal(outs[2][0][:500], r_ids[:500]) and torch.equal(outs[2][1][:500], r_d[:500])
+    gix.close()
