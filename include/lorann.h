@@ -248,6 +248,19 @@ enum { LORANN_RERANK_F32 = 0, LORANN_RERANK_F16 = 1, LORANN_RERANK_NONE = 2 };
 int lorann_set_rerank(lorann_index *ix, int32_t mode);
 
 /*
+ * lorann_set_rerank_screening - whether the re-rank may read all candidates from the half-precision copy first and only those that an
+ * error bound cannot exclude from the rows it takes its distances from.  The results are the same in every mode.
+ *   LORANN_RERANK_SCREEN_AUTO    (default) where it pays: k <= m / 4, and few enough candidates left by the bound - estimated by a search of
+ *                                256 corpus rows when the index is loaded (or its step sizes or re-rank mode change);
+ *   LORANN_RERANK_SCREEN_ALWAYS  whatever that estimate says;
+ *   LORANN_RERANK_SCREEN_NEVER   not at all; the copy is freed unless LORANN_RERANK_F16 reads it (a graph captured earlier must not be replayed).
+ * The copy is made again by the other two if it takes no more than a quarter of the free memory.  Waits for the index's searches in flight.
+ * Errors: LORANN_E_INVAL for an unknown mode.
+ */
+enum { LORANN_RERANK_SCREEN_AUTO = 0, LORANN_RERANK_SCREEN_ALWAYS = 1, LORANN_RERANK_SCREEN_NEVER = 2 };
+int lorann_set_rerank_screening(lorann_index *ix, int32_t mode);
+
+/*
  * Intermediate results of one search, for verification against a reference implementation.  Every pointer
  * may be NULL (skipped) and may be a host or device pointer.  Layouts, with slot = query * w + rank:
  */
@@ -305,6 +318,10 @@ int64_t lorann_profile_fallback_queries(lorann_index *ix);
  * bytes the gather kernel requests.  Waits for all work on the index.  -1: ix is NULL, or the latest batch did not
  * take the grouped re-rank. */
 int64_t lorann_profile_gather_rows(lorann_index *ix);
+
+/* How that batch shared its rows: queries per group (0: it did not), and whether the rows were the half-precision copy's (the screened
+ * re-rank, 1) or those the distances are taken from (0).  Either pointer may be NULL.  Errors: LORANN_E_INVAL for a NULL index. */
+int lorann_profile_gather_plan(lorann_index *ix, int32_t *group_queries, int32_t *screened);
 
 #ifdef __cplusplus
 }

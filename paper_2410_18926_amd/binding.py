@@ -25,10 +25,12 @@ LORANN_OK, LORANN_E_INVAL, LORANN_E_NOMEM, LORANN_E_DEVICE, LORANN_E_UNSUPPORTED
 
 EXPORTS = ["lorann_load_index", "lorann_load_index_file", "lorann_search", "lorann_search_async", "lorann_free_index", "lorann_last_error", "lorann_set_stream",
            "lorann_search_stages", "lorann_profile_enable", "lorann_profile_get", "lorann_set_exact_selection", "lorann_set_screen_mode",
-           "lorann_profile_fallback_queries", "lorann_set_rerank", "lorann_set_column_scales", "lorann_set_first_rows", "lorann_search_lane", "lorann_lane_join", "lorann_set_gather_turns", "lorann_search_noalloc", "lorann_profile_gather_rows"]
+           "lorann_profile_fallback_queries", "lorann_set_rerank", "lorann_set_column_scales", "lorann_set_first_rows", "lorann_search_lane", "lorann_lane_join", "lorann_set_gather_turns", "lorann_search_noalloc", "lorann_profile_gather_rows",
+           "lorann_set_rerank_screening", "lorann_profile_gather_plan"]
 NOALLOC_SCRATCH_BYTES = 32 << 20
 LANES = 4
 RERANK_F32, RERANK_F16, RERANK_NONE = 0, 1, 2
+RERANK_SCREEN_AUTO, RERANK_SCREEN_ALWAYS, RERANK_SCREEN_NEVER = 0, 1, 2
 SCREEN_AUTO, SCREEN_MATRIX, SCREEN_DIGEST = 0, 1, 2
 
 
@@ -90,6 +92,10 @@ def lib() -> C.CDLL:
         L.lorann_lane_join.argtypes = [vp, i32]
         L.lorann_set_rerank.restype = C.c_int
         L.lorann_set_rerank.argtypes = [vp, i32]
+        L.lorann_set_rerank_screening.restype = C.c_int
+        L.lorann_set_rerank_screening.argtypes = [vp, i32]
+        L.lorann_profile_gather_plan.restype = C.c_int
+        L.lorann_profile_gather_plan.argtypes = [vp, C.POINTER(i32), C.POINTER(i32)]
         L.lorann_profile_enable.restype = C.c_int
         L.lorann_profile_enable.argtypes = [vp, i32]
         L.lorann_profile_fallback_queries.restype = C.c_int64
@@ -285,6 +291,11 @@ class Index:
         """RERANK_F32 (default), RERANK_F16 (half-precision copy of the corpus) or RERANK_NONE (no re-ranking step)."""
         _check(lib().lorann_set_rerank(self._h, int(mode)))
 
+    def set_rerank_screening(self, mode: int):
+        """RERANK_SCREEN_AUTO (default), RERANK_SCREEN_ALWAYS or RERANK_SCREEN_NEVER (frees the half-precision copy): same results, other
+        time and memory."""
+        _check(lib().lorann_set_rerank_screening(self._h, int(mode)))
+
     def profile_enable(self, on=True):
         """True / 1: every kernel; 2: only the re-rank gather kernel; False / 0: off."""
         _check(lib().lorann_profile_enable(self._h, int(on)))
@@ -295,6 +306,12 @@ class Index:
     def profile_gather_rows(self) -> int:
         """Rows the grouped re-rank of the latest lane-0 batch fetched (-1: it did not run)."""
         return int(lib().lorann_profile_gather_rows(self._h))
+
+    def profile_gather_plan(self):
+        """(queries per group, screened) of the re-rank of the latest lane-0 batch; (0, False): no rows were shared."""
+        g, sc = C.c_int32(0), C.c_int32(0)
+        _check(lib().lorann_profile_gather_plan(self._h, C.byref(g), C.byref(sc)))
+        return g.value, bool(sc.value)
 
     def profile_get(self) -> dict:
         """{kernel name: (total ms, launches)} since profiling was enabled."""

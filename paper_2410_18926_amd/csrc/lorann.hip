@@ -107,16 +107,18 @@ struct Workspace {
     DevBuf smin, thr, hit_val, hit_grp, hit_cnt;      // screening without the matrix of approximate values
     DevBuf submax;                                    // quarter maxima of large clusters
     DevBuf qhalf, qstat, u_meta;                      // screened re-rank (its other lists share u_row, u_pos, u_count, rdist and rccount)
+    DevBuf kept;                                      // sample search at load only: candidates read in full
     hipStream_t stream = nullptr;          // lanes >= 1: created on first use, default priority
     hipEvent_t fork = nullptr, join = nullptr;
     hipEvent_t gather_done = nullptr;      // recorded after this lane's latest re-rank gather
     Arena* arena = nullptr;                // set: every buffer is a slice of this fixed region, nothing is allocated or freed
-    int64_t last_ngroups = 0;              // groups of the latest grouped re-rank on this workspace (0: none)
+    int64_t last_ngroups = 0;              // groups of the latest re-rank with shared rows on this workspace (0: none)
+    int32_t last_group = 0, last_screened = 0;       // queries per group, whether the rows were the binary16 copy's
     void release() {
         if (arena) return;
         DevBuf* bufs[] = {&qproj, &qbf, &q8, &dx, &gscore, &sel, &count, &rank_in_bucket, &qrank, &qorder, &qorder2, &off0, &base_tab, &bucket_off, &tile_off,
                           &unit_off, &slot_of_pos, &pos_of_slot, &Z, &sigma, &rho0, &cand, &tau, &n_kept, &fb_list, &pmax, &voff, &qkey, &u_row, &u_mask, &u_pos, &u_count, &rdist, &rcid, &rccount,
-                          &smin, &thr, &hit_val, &hit_grp, &hit_cnt, &submax, &qhalf, &qstat, &u_meta};
+                          &smin, &thr, &hit_val, &hit_grp, &hit_cnt, &submax, &qhalf, &qstat, &u_meta, &kept};
         for (DevBuf* b : bufs) b->release();
         if (fork) (void)hipEventDestroy(fork);
         if (gather_done) (void)hipEventDestroy(gather_done);
@@ -182,6 +184,9 @@ struct lorann_index {
     _Float16* corpus_h = nullptr;   // [n][ld_h] binary16 copy of the corpus (NULL: it does not fit, or binary16 cannot hold the values)
     int32_t ld_h = 0;               // its row stride
     HalfStats half{};               // what the copy lost
+    float screen_keeps[2] = {-1.0f, -1.0f};      // share of the candidates beyond the k best that the screened re-rank has to read in full, float
+                                                 // and binary16 rows, from a sample search (-1: not measured, taken as 0)
+    int32_t rerank_screening = LORANN_RERANK_SCREEN_AUTO;
     int32_t rerank_mode = LORANN_RERANK_F32;
     int64_t* ids = nullptr;         // [n] or NULL
     float* sqnorm = nullptr;        // [n] (Euclidean)
@@ -259,6 +264,13 @@ int make_half_corpus(lorann_index* ix, bool required) {
     if (!required) return LORANN_OK;
     if (e != hipSuccess) return fail(e == hipErrorOutOfMemory ? LORANN_E_NOMEM : LORANN_E_DEVICE, "building the half-precision corpus failed: %s", hipGetErrorString(e));
     return fail(LORANN_E_UNSUPPORTED, "the corpus holds values beyond the binary16 range (largest magnitude %g)", (double)hs.abs_max);
+}
+
+// The copy is given back where neither the rows nor the screening are taken from it (no search may be in flight).
+void drop_half_corpus(lorann_index* ix) {
+    if (!ix->corpus_h || ix->rerank_screening != LORANN_RERANK_SCREEN_NEVER || ix->rerank_mode == LORANN_RERANK_F16) return;
+    (void)hipFree(ix->corpus_h);
+    ix->corpus_h = nullptr;
 }
 
 __global__ void k_pad_codes(const int8_t* __restrict__ B, int8_t* __restrict__ Bp, int64_t n, int r, int r_pad) {
@@ -376,6 +388,19 @@ struct ChunkPlan {
     int64_t ngroups;
 };
 
+// Share of the m candidates, read in full behind the screening, up to which it pays: against the gather of full rows that queries share, and
+// against the re-rank of one query per block, which shares nothing.  Full-width / screened time by that share, 10 000 queries, float
+// rows: 1M x 768-like, m = 200: 1.56 at 0.05, 1.37 at 0.10, 1.21 at 0.15, 1.00 at 0.25 (binary16 rows 1.19, 1.11, 1.06, 0.98); d = 256 with a
+// mean of 8 and 12 standard deviations: 1.01 at 0.24, 0.74 at 0.49.  One query per block (m = 600): 1.74 at 0.22, 2.33 at 0.47, 0.85 at 1.
+constexpr float kScreenPaysShared = 0.2f, kScreenPaysAlone = 0.8f;
+
+// The share is the k best and what the bound cannot tell from them: hardly anything where the candidates' spread is of the order of their
+// length, everything where the mean of the corpus is many times its spread, or where one row is much longer than the others.
+bool screening_pays(const lorann_index* ix, int k, int m, bool grouped) {
+    const float keeps = std::max(0.0f, ix->screen_keeps[ix->rerank_mode == LORANN_RERANK_F16]);
+    return (float)k + keeps * (float)(m - k) <= (grouped ? kScreenPaysShared : kScreenPaysAlone) * (float)m;
+}
+
 ChunkPlan plan_chunk(const lorann_index* ix, int64_t nq, int k, int w, int m, bool allow_quarters = true, bool allow_screened = true) {
     ChunkPlan pl;
     const int L = ix->L;
@@ -414,8 +439,8 @@ ChunkPlan plan_chunk(const lorann_index* ix, int64_t nq, int k, int w, int m, bo
                    quarters_suffice(ix->quarters, pl.sub_chunks);
     if (!pl.wave_walk) pl.sub_chunks = 0;
     pl.handful = pl.small && pl.grouped && nq <= 8 && ix->d % 4 == 0 && ix->d <= 1024 && k <= 64;
-    // The screened re-rank reads all candidates at half width and about k of them in full: it pays while k is a small part of m
-    // (a row read at half width is shared by about two queries, one read in full is not, so up to k = m / 4).  A few dozen queries are
+    // The screened re-rank reads all candidates at half width and about k of them in full: it pays while those are a small part of m
+    // (a row read at half width is shared by about two queries, one read in full is not).  A few dozen queries are
     // bound by the latency of the three launches, where the grouped re-rank's are shorter (64 queries: 115 us against 118).
     const int ld = half_stride(ix->d);
     pl.screen_gq = std::min(pl.small ? 1 : screen_group_size(m), (64 * 1024) / (2 * ld + 16));
@@ -425,7 +450,8 @@ ChunkPlan plan_chunk(const lorann_index* ix, int64_t nq, int k, int w, int m, bo
     // 4096; 1024 over 1024 42 -> 17, 59 -> 61.  Not beyond: 1000 queries over 64 clusters 14 -> 12, but 10 -> 13 for twice the rows;
     // 16 384 queries over 16 384 clusters in groups of 4 lose (51 -> 69).
     if (!pl.small && nq <= 2 * (int64_t)L) pl.screen_gq = (int)std::min<int64_t>(pl.screen_gq, std::max<int64_t>(4, (nq + 1023) / 1024));
-    pl.screened = allow_screened && ix->rerank_mode != LORANN_RERANK_NONE && !ix->force_exact && !(pl.small && pl.grouped) && ix->corpus_h && pl.screen_gq > 0 && 4 * k <= m;
+    pl.screened = allow_screened && ix->rerank_mode != LORANN_RERANK_NONE && !ix->force_exact && !(pl.small && pl.grouped) && ix->corpus_h && pl.screen_gq > 0 && 4 * k <= m &&
+                  (ix->rerank_screening == LORANN_RERANK_SCREEN_ALWAYS || (ix->rerank_screening == LORANN_RERANK_SCREEN_AUTO && screening_pays(ix, k, m, pl.grouped)));
     pl.screen_stride = (pl.screen_gq * m + 15) & ~15;
     if (pl.screened) pl.grouped = false;
     // (small batches: a group per query - nothing to share, and the union and the gather of a group are latency chains)
@@ -525,6 +551,7 @@ int launch_screened_rerank(lorann_index* ix, Workspace& ws, hipStream_t s, const
     ra.qhalf = ws.qhalf.as<_Float16>(); ra.qstat = ws.qstat.as<float4>(); ra.u_row = ws.u_row.as<int32_t>(); ra.u_meta = ws.u_meta.as<uint32_t>();
     ra.entry = ws.u_pos.as<uint16_t>(); ra.qgroup = ws.rccount.as<int32_t>(); ra.u_count = ws.u_count.as<int32_t>(); ra.approx = ws.rdist.as<float>(); ra.out_ids = d_ids; ra.out_dists = d_dists;
     ra.nq = (int)nq; ra.d = d; ra.ld = ix->ld_h; ra.m = m; ra.k = k; ra.gq = pl.screen_gq; ra.gstride = pl.screen_stride; ra.metric = ix->metric;
+    ra.kept = ws.kept.as<int32_t>();
     // (rounded up; half rows: the stored row is what counts, only the subnormal elements may be lost to the matrix core)
     ra.norm = (half_rows ? hs.norm + hs.err : hs.norm) * 1.0001f;
     ra.err = (half_rows ? hs.lost : hs.err) * 1.0001f;
@@ -538,7 +565,7 @@ int launch_screened_rerank(lorann_index* ix, Workspace& ws, hipStream_t s, const
     const int max_slices = std::min(16, (pl.screen_gq * m + 63) / 64);
     const int64_t group_bytes = (int64_t)pl.screen_gq * m * ix->ld_h;
     while (ra.slices < max_slices && (ra.slices * pl.ngroups < 4096 || (ra.slices * pl.ngroups < 8192 && group_bytes / (ra.slices + 1) >= (128 << 10)))) ++ra.slices;
-    ws.last_ngroups = pl.ngroups;
+    ws.last_ngroups = pl.ngroups; ws.last_group = pl.screen_gq; ws.last_screened = 1;
     {
         Prof p(ix, K_UNION, s);
         hipLaunchKernelGGL(k_screen_union, dim3((unsigned)pl.ngroups), dim3(kScreenUnionThreads), pl.screen_gq > 1 ? (size_t)kScreenSlots * 8 : 0, s, ra);
@@ -591,6 +618,7 @@ int search_chunk(lorann_index* ix, Workspace& ws, hipStream_t s, const float* dQ
     const int64_t npairs = nq * w;
     ChunkPlan pl;
     { const int rc = plan_and_reserve(ix, ws, nq, k, w, m, pl); if (rc) return rc; }
+    ws.last_ngroups = 0;
     const bool mixed = pl.mixed;
 
     const float* qp = dQ;   // projected queries
@@ -884,7 +912,6 @@ int search_chunk(lorann_index* ix, Workspace& ws, hipStream_t s, const float* dQ
             ga.Q = dQ; ga.corpus = half_rows ? (const void*)ix->corpus_h : (const void*)ix->corpus; ga.ids = ix->ids; ga.cand = ws.cand.as<int32_t>();
             ga.dist = ws.rdist.as<float>(); ga.cid = ws.rcid.as<int64_t>(); ga.ccount = ws.rccount.as<int32_t>();
             ga.out_ids = d_ids; ga.out_dists = d_dists; ga.nq = (int)nq; ga.d = d; ga.ld = ld_rows; ga.m = m; ga.k = k;
-            ws.last_ngroups = 0;
             const int slices = std::min(16, (m + 7) / 8);
             const int nv = (d / 4 + 63) / 64;
             Prof p(ix, K_RERANK, s);
@@ -917,7 +944,7 @@ int search_chunk(lorann_index* ix, Workspace& ws, hipStream_t s, const float* dQ
         ga.out_ids = d_ids; ga.out_dists = d_dists; ga.nq = (int)nq; ga.d = d; ga.ld = ld_rows; ga.m = m; ga.k = k;
         ga.gq = pl.small ? 1 : kGroupQ;
         ga.ht = rerank_group_ht(ga.gq, m);
-        ws.last_ngroups = ngroups;
+        ws.last_ngroups = ngroups; ws.last_group = ga.gq; ws.last_screened = 0;
         // enough gather blocks to keep every CU evenly busy: about 2 MiB of rows per block at most
         ga.slices = (int)std::min<int64_t>(16, std::max<int64_t>(1, ((int64_t)gm * d * 4 / 2) / (2 << 20) + 1));
         while ((int64_t)ga.slices * ngroups < 4096 && ga.slices < 16) ++ga.slices;
@@ -1040,6 +1067,42 @@ int search_chunk(lorann_index* ix, Workspace& ws, hipStream_t s, const float* dQ
             if (e != hipSuccess) return fail(LORANN_E_DEVICE, "score dump failed: %s", hipGetErrorString(e));
         }
     }
+    return LORANN_OK;
+}
+
+// What the screened re-rank's bound keeps of this index's candidates in the current re-rank mode, from a search of 256 of its rows
+// (buffers of its own, given back; nothing is measured - and the screening taken as useful - where no such search can run).
+int measure_screening(lorann_index* ix) {
+    if (ix->rerank_mode == LORANN_RERANK_NONE || !ix->corpus_h) return LORANN_OK;
+    float& keeps = ix->screen_keeps[ix->rerank_mode == LORANN_RERANK_F16];
+    if (keeps >= 0.0f) return LORANN_OK;
+    const int count = (int)std::min<int64_t>(256, ix->n), k = 10, m = 200, w = std::min(32, (int)ix->L);
+    if (count <= kSmallPathQueries || ix->n < 2 * m || (size_t)ix->d * 4 + 256 * 12 > 64 * 1024) return LORANN_OK;
+    const std::string said = g_err;
+    const int32_t turns = ix->gather_turns, exact = ix->force_exact, screening = ix->rerank_screening;
+    const bool prof = ix->prof_on;
+    ix->gather_turns = 0; ix->force_exact = 0; ix->prof_on = false; ix->rerank_screening = LORANN_RERANK_SCREEN_ALWAYS;
+    Workspace ws;
+    DevBuf q, ids, dists;
+    std::vector<int32_t> kept((size_t)count, k);
+    int rc = q.reserve((size_t)count * ix->d * 4);
+    if (rc == LORANN_OK) rc = ids.reserve((size_t)count * k * 8);
+    if (rc == LORANN_OK) rc = dists.reserve((size_t)count * k * 4);
+    if (rc == LORANN_OK) rc = ws.kept.reserve((size_t)count * 4);
+    if (rc == LORANN_OK && plan_chunk(ix, count, k, w, m).screened) {
+        hipLaunchKernelGGL(k_sample_rows, dim3((unsigned)count), dim3(256), 0, ix->stream, ix->corpus, q.as<float>(), ix->n, ix->d, count);
+        rc = search_chunk(ix, ws, ix->stream, q.as<float>(), count, k, w, m, ids.as<int64_t>(), dists.as<float>(), nullptr, 0, nullptr);
+        if (rc == LORANN_OK && (hipStreamSynchronize(ix->stream) != hipSuccess || ws.last_screened == 0 ||
+                                hipMemcpy(kept.data(), ws.kept.p, kept.size() * 4, hipMemcpyDeviceToHost) != hipSuccess)) rc = LORANN_E_DEVICE;
+    }
+    ix->gather_turns = turns; ix->force_exact = exact; ix->prof_on = prof; ix->rerank_screening = screening;
+    DevBuf* bufs[] = {&q, &ids, &dists};
+    for (DevBuf* b : bufs) b->release();
+    ws.release();
+    if (rc != LORANN_OK) { g_err = said; (void)hipGetLastError(); return LORANN_OK; }
+    double beyond = 0.0;
+    for (int32_t c : kept) beyond += std::max(0, c - k);
+    keeps = (float)(beyond / ((double)(m - k) * count));
     return LORANN_OK;
 }
 
@@ -1297,7 +1360,7 @@ int lorann_load_index(lorann_index** out, int32_t metric, int64_t n, int32_t d, 
             HIP_TRY(hipDeviceSynchronize());
         }
         if ((e = make_half_corpus(ix, false))) return e;
-        return LORANN_OK;
+        return measure_screening(ix);
     };
     rc = body();
     if (rc != LORANN_OK) { std::string keep = g_err; free_all(ix); g_err = keep; return rc; }
@@ -1434,7 +1497,8 @@ int lorann_set_column_scales(lorann_index* ix, const float* scale_A_columns, con
         if (ix->B_first) (void)hipFree(ix->B_first);
         ix->A_first = ix->B_first = nullptr;
     }
-    return LORANN_OK;
+    ix->screen_keeps[0] = ix->screen_keeps[1] = -1.0f;    // other candidates
+    return measure_screening(ix);
 }
 
 int lorann_set_first_rows(lorann_index* ix, const float* first_row_A, const float* first_row_B) {
@@ -1460,7 +1524,8 @@ int lorann_set_first_rows(lorann_index* ix, const float* first_row_A, const floa
     if (ix->A_first) (void)hipFree(ix->A_first);
     if (ix->B_first) (void)hipFree(ix->B_first);
     ix->A_first = na; ix->B_first = nb;
-    return LORANN_OK;
+    ix->screen_keeps[0] = ix->screen_keeps[1] = -1.0f;    // other candidates
+    return measure_screening(ix);
 }
 
 int lorann_set_rerank(lorann_index* ix, int32_t mode) {
@@ -1469,7 +1534,21 @@ int lorann_set_rerank(lorann_index* ix, int32_t mode) {
     { const int rc = sync_all(ix); if (rc) return rc; }   // searches in flight keep the mode they were enqueued with
     if (mode == LORANN_RERANK_F16) { const int rc = make_half_corpus(ix, true); if (rc) return rc; }
     ix->rerank_mode = mode;
-    return LORANN_OK;
+    drop_half_corpus(ix);
+    return measure_screening(ix);
+}
+
+int lorann_set_rerank_screening(lorann_index* ix, int32_t mode) {
+    if (!ix) return fail(LORANN_E_INVAL, "index is NULL");
+    if (mode != LORANN_RERANK_SCREEN_AUTO && mode != LORANN_RERANK_SCREEN_ALWAYS && mode != LORANN_RERANK_SCREEN_NEVER) return fail(LORANN_E_INVAL, "unknown re-rank screening mode %d", (int)mode);
+    { const int rc = sync_all(ix); if (rc) return rc; }   // searches in flight keep the path they were enqueued with
+    ix->rerank_screening = mode;
+    if (mode == LORANN_RERANK_SCREEN_NEVER) {
+        drop_half_corpus(ix);
+        return LORANN_OK;
+    }
+    { const int rc = make_half_corpus(ix, false); if (rc) return rc; }
+    return measure_screening(ix);
 }
 
 int lorann_set_exact_selection(lorann_index* ix, int32_t on) {
@@ -1512,6 +1591,14 @@ int64_t lorann_profile_gather_rows(lorann_index* ix) {
     int64_t tot = 0;
     for (int32_t v : h) tot += v;
     return tot;
+}
+
+int lorann_profile_gather_plan(lorann_index* ix, int32_t* group_queries, int32_t* screened) {
+    if (!ix) return fail(LORANN_E_INVAL, "index is NULL");
+    const Workspace& ws = ix->ws[0];
+    if (group_queries) *group_queries = ws.last_ngroups > 0 ? ws.last_group : 0;
+    if (screened) *screened = ws.last_ngroups > 0 ? ws.last_screened : 0;
+    return LORANN_OK;
 }
 
 int lorann_profile_get(lorann_index* ix, lorann_kernel_time* out, int32_t cap) {

@@ -108,6 +108,12 @@ __global__ __launch_bounds__(256) void k_corpus_to_half_rows(const float* __rest
     if (threadIdx.x < 7) atomicMax(&st[threadIdx.x], s_mx[threadIdx.x]);
 }
 
+// Rows of the corpus as queries, evenly spaced: dst[i] = row (2 i + 1) n / (2 count).  grid = count, block = 256.
+__global__ __launch_bounds__(256) void k_sample_rows(const float* __restrict__ corpus, float* __restrict__ dst, int64_t n, int d, int count) {
+    const size_t row = (size_t)((2 * (int64_t)blockIdx.x + 1) * n / (2 * (int64_t)count));
+    for (int i = threadIdx.x; i < d; i += 256) dst[(size_t)blockIdx.x * d + i] = corpus[row * d + i];
+}
+
 struct ScreenRerankArgs {
     const float* Q;              // [nq][d]
     const void* corpus;          // rows the exact dissimilarities are taken from: float [n][d] or binary16 [n][ld]
@@ -128,6 +134,7 @@ struct ScreenRerankArgs {
                                  //                    bound of the exact one
     int64_t* out_ids;            // [nq][k]
     float* out_dists;            // [nq][k]
+    int32_t* kept;               // [nq] candidates that were read in full, or NULL
     int nq, d, ld, m, k, gq, slices;
     int gstride;                 // entries of a group's lists: gq * m rounded up to whole tiles of 16
     int metric;                  // 0 inner product, 1 squared Euclidean, 2 cosine
@@ -493,6 +500,7 @@ __global__ __launch_bounds__(256) void k_screen_finish(ScreenRerankArgs a) {
     }
     meet();
     const int c = s_cnt[sub];
+    if (a.kept && lane == 0 && w0 == 0) a.kept[q] = c;
     auto finish = [&](int i, float acc) {       // lane 63 records the distance of survivor i
         float dist;
         if (L2) dist = acc;

@@ -46,7 +46,9 @@ def test_same_bits_as_the_plain_rerank(B, d, metric, nq, m, k, half):
     gix = B.Index(**ix)
     if half:
         gix.set_rerank(B.RERANK_F16)
+    gix.set_rerank_screening(B.RERANK_SCREEN_ALWAYS)
     s_ids, s_d = gix.search(q, k, 6, m)
+    assert gix.profile_gather_plan()[1] == (nq > 64 or m > 512 or d > 1536)      # (small batches share full rows where they can)
     gix.set_exact_selection(True)
     e_ids, e_d = gix.search(q, k, 6, m)
     gix.set_exact_selection(False)
@@ -70,7 +72,9 @@ def test_queries_that_are_no_numbers_keep_every_candidate(B):
     q[50] *= np.float32(1e30)
     q[51] *= np.float32(1e-30)
     gix = B.Index(**ix)
+    gix.set_rerank_screening(B.RERANK_SCREEN_ALWAYS)
     ids, dist = gix.search(q, 5, 3, 100)
+    assert gix.profile_gather_plan()[1]
     ref_ids, ref_d = gix.search(clean, 5, 3, 100)
     good = np.setdiff1d(np.arange(70), [11, 40, 50, 51])
     np.testing.assert_array_equal(ids[good], ref_ids[good])
@@ -91,7 +95,9 @@ def test_few_queries_per_cluster(B, nq):
     ix = _random_index(rng, n=9000, d=48, L=L, r=8, metric=nq % 3, dp=32)
     q = rng.normal(size=(nq, 48)).astype(np.float32)
     gix = B.Index(**ix)
+    gix.set_rerank_screening(B.RERANK_SCREEN_ALWAYS)
     s_ids, s_d = gix.search(q, 10, 40, 100)
+    assert gix.profile_gather_plan() == (4 if nq <= 4096 else 5, True) or nq > 2 * L
     gix.set_exact_selection(True)
     e_ids, e_d = gix.search(q, 10, 40, 100)
     np.testing.assert_array_equal(s_ids, e_ids)
@@ -116,7 +122,9 @@ def test_distances_that_overflow_tie_by_id(B, metric, scales, half):
     gix = B.Index(**ix)
     if half:
         gix.set_rerank(B.RERANK_F16)
+    gix.set_rerank_screening(B.RERANK_SCREEN_ALWAYS)
     s_ids, s_d = gix.search(q, 10, 4, 100)
+    assert gix.profile_gather_plan()[1]
     gix.set_exact_selection(True)
     e_ids, e_d = gix.search(q, 10, 4, 100)
     gix.close()
@@ -154,4 +162,62 @@ def test_search_without_room_for_the_screening_lists(B, metric, nq, m, w):
     for ids, d in outs[:2]:
         assert torch.equal(ids, r_ids) and torch.equal(d, r_d)
     assert torch.equal(outs[2][0][:500], r_ids[:500]) and torch.equal(outs[2][1][:500], r_d[:500])
+    gix.close()
+
+
+@pytest.mark.parametrize("what,metric,screened", [("plain", 0, True), ("plain", 1, True), ("plain", 2, True), ("mean", 0, False), ("mean", 1, False),
+                                                  ("one long row", 0, False), ("one row near zero", 1, False)])
+@pytest.mark.parametrize("half", [False, True])
+def test_screening_is_left_out_where_its_bound_keeps_everything(B, what, metric, screened, half):
+    """A mean of a thousand times the spread, one row a thousand times as long as the others (inner product), one row whose elements are all
+    subnormal in binary16 (Euclidean): the bound excludes hardly a candidate, which the search of a sample at load finds out.  The three
+    settings give the same results."""
+    rng = np.random.default_rng(17 + metric)
+    ix = _random_index(rng, n=20_000, d=96, L=12, r=8, metric=metric, dp=32)
+    q = rng.normal(size=(300, 96)).astype(np.float32)
+    if what == "mean":
+        ix["corpus"] = ix["corpus"] + np.float32(1000)
+        q = q + np.float32(1000)
+    elif what == "one long row":
+        ix["corpus"][12_345] *= np.float32(1000)
+    elif what == "one row near zero":
+        ix["corpus"][12_345] = np.float32(3e-5) * np.sign(ix["corpus"][12_345])
+    gix = B.Index(**ix)
+    if half:
+        gix.set_rerank(B.RERANK_F16)
+    a_ids, a_d = gix.search(q, 10, 5, 200)
+    assert gix.profile_gather_plan()[1] == screened
+    for mode in (B.RERANK_SCREEN_ALWAYS, B.RERANK_SCREEN_NEVER):
+        gix.set_rerank_screening(mode)
+        ids, d = gix.search(q, 10, 5, 200)
+        assert gix.profile_gather_plan()[1] == (mode == B.RERANK_SCREEN_ALWAYS)
+        np.testing.assert_array_equal(ids, a_ids)
+        np.testing.assert_array_equal(d, a_d)
+    gix.close()
+
+
+def test_the_half_precision_copy_is_given_back(B):
+    """NEVER frees the copy, the other settings and the half-precision re-rank make it again."""
+    rng = np.random.default_rng(3)
+    ix = _random_index(rng, n=200_000, d=128, L=40, r=8, metric=1)
+    q = rng.normal(size=(100, 128)).astype(np.float32)
+    gix = B.Index(**ix)
+    copy = 200_000 * 128 * 2
+    ids, d = gix.search(q, 10, 5, 100)
+    free = torch.cuda.mem_get_info()[0]
+    gix.set_rerank_screening(B.RERANK_SCREEN_NEVER)
+    assert torch.cuda.mem_get_info()[0] - free > 0.9 * copy
+    n_ids, n_d = gix.search(q, 10, 5, 100)
+    gix.set_rerank(B.RERANK_F16)
+    h_ids, _ = gix.search(q, 10, 5, 100)
+    assert (h_ids == ids).mean() > 0.9 and not gix.profile_gather_plan()[1]
+    gix.set_rerank(B.RERANK_F32)
+    assert torch.cuda.mem_get_info()[0] - free > 0
+    gix.set_rerank_screening(B.RERANK_SCREEN_AUTO)
+    a_ids, a_d = gix.search(q, 10, 5, 100)
+    for i, x in ((n_ids, n_d), (a_ids, a_d)):
+        np.testing.assert_array_equal(i, ids)
+        np.testing.assert_array_equal(x, d)
+    with pytest.raises(B.LorannError):
+        gix.set_rerank_screening(3)
     gix.close()
