@@ -158,10 +158,10 @@ int lorann_search_noalloc(lorann_index *ix, const float *queries, int64_t nq, in
  * After it, work enqueued on the index's stream - or a synchronisation of that stream - sees the lane's results. */
 int lorann_lane_join(lorann_index *ix, int32_t lane);
 
-/* The re-rank gather of one batch alone saturates HBM, so by default the gathers of different lanes take turns (each
- * waits, on the device, for the previous lane's gather) while all other stages of the lanes overlap freely; every
- * gather then runs at its full rate.  on = 0 lets gathers overlap as well: each launch takes longer, the throughput of
- * a loop over several lanes was measured a few percent higher.  Waits for all lanes first. */
+/* By default the re-rank gathers of different lanes take turns (each waits, on the device, for the previous lane's
+ * gather) while all other stages of the lanes overlap freely; every gather then runs at its full rate.  on = 0 lets
+ * gathers overlap as well: each launch takes longer, the throughput of a loop over four lanes was measured 5 % higher
+ * at 1M x 768 and 1.5 % at 1M x 1024 (batches of 10 000).  Waits for all lanes first. */
 int lorann_set_gather_turns(lorann_index *ix, int32_t on);
 
 /* Release an index and its workspaces.  NULL is ignored. */
