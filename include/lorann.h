@@ -235,7 +235,8 @@ int lorann_set_first_rows(lorann_index *ix, const float *first_row_A, const floa
  *                       re-rank over the rounded rows; candidates are unaffected.  The copy (rows padded to a
  *                       multiple of 32 elements, 2 bytes each) is made when the index is loaded if it takes no more than
  *                       a quarter of the GPU's free memory then, else by the first call that selects this mode, and
- *                       lives as long as the index (the float mode screens its candidates with it).  LORANN_E_UNSUPPORTED
+ *                       lives as long as the index (the float mode screens its candidates with it) unless
+ *                       lorann_set_rerank_screening gives it back.  LORANN_E_UNSUPPORTED
  *                       if a corpus value is not finite or exceeds 65504 in magnitude (mode unchanged).
  *   LORANN_RERANK_NONE  no re-ranking step (Sec. 7.1 memory usage, App. D.3): the k points of highest estimated
  *                       score are returned (ties at the boundary toward the lower corpus row), nearest first by

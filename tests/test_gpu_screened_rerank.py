@@ -62,6 +62,33 @@ def test_same_bits_as_the_plain_rerank(B, d, metric, nq, m, k, half):
     gix.close()
 
 
+# beyond 2048 queries one wavefront finishes a query (m <= 512; four above): every register slice, rows that are and are not a multiple of
+# four elements, both candidate budgets, a ragged last block
+WIDE = [(50, 2, 257, 10), (128, 1, 100, 10), (255, 0, 200, 40), (301, 1, 300, 7), (516, 0, 256, 12), (768, 0, 200, 10), (1023, 1, 512, 60), (1024, 2, 300, 10),
+        (1028, 1, 200, 10), (2001, 0, 60, 15), (96, 0, 700, 100)]
+
+
+@pytest.mark.parametrize("half", [False, True])
+@pytest.mark.parametrize("d,metric,m,k", WIDE)
+def test_same_bits_in_large_batches(B, d, metric, m, k, half):
+    rng = np.random.default_rng(77 * d + metric)
+    ix = _random_index(rng, n=5000, d=d, L=9, r=8, metric=metric, dp=32)
+    if metric != 2:
+        ix["corpus"] = (ix["corpus"] * np.exp(rng.normal(size=(5000, 1)) * 0.5)).astype(np.float32)
+    ix["corpus"][1::2] = ix["corpus"][0::2] * np.float32(1 + 2.0 ** -9 if metric == 0 else 1)      # near-ties and ties
+    q = torch.from_numpy(rng.normal(size=(2051, d)).astype(np.float32)).cuda()
+    gix = B.Index(**ix)
+    if half:
+        gix.set_rerank(B.RERANK_F16)
+    gix.set_rerank_screening(B.RERANK_SCREEN_ALWAYS)
+    s_ids, s_d = gix.search(q, k, 4, m)
+    assert gix.profile_gather_plan()[1]
+    gix.set_exact_selection(True)
+    e_ids, e_d = gix.search(q, k, 4, m)
+    gix.close()
+    assert torch.equal(s_ids, e_ids) and torch.equal(s_d, e_d)
+
+
 def test_queries_that_are_no_numbers_keep_every_candidate(B):
     """An infinite or NaN query gives bounds that are no numbers: nothing may be dropped for the other queries of its group, and the call ends."""
     rng = np.random.default_rng(5)
