@@ -95,9 +95,9 @@ def gather_accounting(gix, wl, queries, k, w, m, elem_bytes):
     """Bytes of the re-rank gather for one batch, taken from this run (lane 0, synchronous):
       algorithmic  every query gathers its m rows (the method as stated, Sec. 2.2): nq * m * d * elem
       requested    what the gather asks the memory system for: each row once per GROUP of queries that share it
-                   (sum over groups of their distinct rows), the queries, the row lists and the results.  With k <= m / 4 the
-                   gather is the screening one: it reads the library's binary16 copy of the rows, whatever the rows that the
-                   few survivors are read from
+                   (sum over groups of their distinct rows), the queries, the row lists and the results.  The screening
+                   gather reads the library's binary16 copy of the rows, whatever the rows that the few survivors are read
+                   from; which gather ran, and for how many queries at a time, is asked of the library
       floor        each distinct candidate row of the whole batch once - no kernel can read less."""
     nq, d = queries.shape[0], wl.d
     st = gix.search_stages(queries, k, w, m)[2]
@@ -105,12 +105,12 @@ def gather_accounting(gix, wl, queries, k, w, m, elem_bytes):
     valid = int((cand >= 0).sum())
     distinct = int(np.unique(cand[cand >= 0]).size)
     union_rows = gix.profile_gather_rows()
-    screened = union_rows >= 0 and 4 * k <= m
+    group, screened = gix.profile_gather_plan()
     algorithmic = nq * m * d * elem_bytes
     if screened:
         elem_bytes = 2
     acc = {"algorithmic_bytes": algorithmic, "floor_bytes": distinct * d * elem_bytes,
-           "screened": screened, "candidate_rows": valid, "distinct_rows": distinct, "rows_fetched": union_rows if union_rows >= 0 else None}
+           "screened": screened, "group": group, "candidate_rows": valid, "distinct_rows": distinct, "rows_fetched": union_rows if union_rows >= 0 else None}
     if screened:
         # per fetched row: the row (padded to 32 elements), its number and its queries (8 B); per query: the query in binary16;
         # per candidate: the approximate dissimilarity, or its two bounds (Euclidean)
@@ -511,7 +511,7 @@ def main():
         avg_ms = ms / max(1, launches)
         per_step_ms = ms / K if prof_dom.get("rerank", (0, 0))[1] else avg_ms * dom["launches_per_step"]
         acc = gather or {"algorithmic_bytes": nq * m * wl.d * RERANK_ELEM_BYTES.get(args.rerank, 4), "requested_bytes": None,
-                         "floor_bytes": None, "screened": False, "rows_fetched": None, "distinct_rows": None, "candidate_rows": None}
+                         "floor_bytes": None, "screened": False, "group": 0, "rows_fetched": None, "distinct_rows": None, "candidate_rows": None}
         scale_b = nq / min(nq, 32768)            # the accounting pass covers one launch (at most 32768 queries)
         req = acc["requested_bytes"] * scale_b if acc["requested_bytes"] else None
         alg = nq * m * wl.d * RERANK_ELEM_BYTES.get(args.rerank, 4)
@@ -520,7 +520,7 @@ def main():
         traffic = tracked_traffic_gb(args.workload, "k_screen_gather" if acc["screened"] else "k_group_gather") if (args.scale == 1.0 and not args.batch and args.rerank == "f32") else None
         roofline = {"kernel": "rerank", "bound": "hbm", "achieved": round(rate, 1), "peak": PEAK_HBM_GBS, "unit": "GB/s",
                     "frac": round(rate / PEAK_HBM_GBS, 4), "avg_ms": round(avg_ms, 5),
-                    "bytes": f"requested by the kernel in this run: each candidate row once, {'as binary16' if acc['screened'] else 'at its stored width'}, per group of {16 if acc['screened'] else 8} queries that share it, plus queries, row lists and results" if req else "algorithmic",
+                    "bytes": f"requested by the kernel in this run: each candidate row once, {'as binary16' if acc['screened'] else 'at its stored width'}, per group of up to {acc['group']} queries that share it, plus queries, row lists and results" if req and acc['group'] else "algorithmic",
                     "requested_gb": round(num / 1e9, 4), "algorithmic_gb": round(alg / 1e9, 4),
                     "algorithmic_rate": round(alg / 1e9 / (per_step_ms / 1e3), 1),
                     "floor_gb": round(acc["floor_bytes"] * scale_b / 1e9, 4) if acc["floor_bytes"] else None,

@@ -38,7 +38,7 @@ typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x4v __attribute__((ext_vector_type(4)));
 
 constexpr int kScreenGroup = 16;          // queries per group: the columns of one matrix-core tile
-constexpr int kScreenEntries = 3276;      // (query, candidate) entries of a group: 0.8 of a 4096-slot table (32 KiB of LDS, 5 blocks per CU)
+constexpr int kScreenEntries = 3276;      // (query, candidate) entries of a group: 0.8 of a 4096-slot table (32 KiB of LDS; four blocks of eight wavefronts fill a CU)
 constexpr int kScreenSlots = 4096;
 constexpr int kScreenUnionThreads = 512;
 constexpr int kScreenPerThread = (kScreenEntries + kScreenUnionThreads - 1) / kScreenUnionThreads;

@@ -524,7 +524,6 @@ __global__ __launch_bounds__(256) void k_select_clusters_screen_wave(ScreenArgs 
             c1 += __popcll(mk);
         }
         if (c1 <= kScreenWaveCap) {                        // uniform
-            if (lane < 2) cand[c1 + lane] = ~0ull;
             lds_sync();
             unsigned long long mine_e[kScreenWaveCap / 64];
 #pragma unroll
