@@ -251,8 +251,8 @@ int lorann_set_rerank(lorann_index *ix, int32_t mode);
 /*
  * lorann_set_rerank_screening - whether the re-rank may read all candidates from the half-precision copy first and only those that an
  * error bound cannot exclude from the rows it takes its distances from.  The results are the same in every mode.
- *   LORANN_RERANK_SCREEN_AUTO    (default) where it pays: k <= m / 4, and few enough candidates left by the bound - estimated by a search of
- *                                256 corpus rows when the index is loaded (or its step sizes or re-rank mode change);
+ *   LORANN_RERANK_SCREEN_AUTO    (default) where it pays: k <= m / 4, and few enough candidates left by the bound - estimated by a search of a
+ *                                few hundred corpus rows when the index is loaded (or its step sizes or re-rank mode change);
  *   LORANN_RERANK_SCREEN_ALWAYS  whatever that estimate says;
  *   LORANN_RERANK_SCREEN_NEVER   not at all; the copy is freed unless LORANN_RERANK_F16 reads it (a graph captured earlier must not be replayed).
  * The copy is made again by the other two if it takes no more than a quarter of the free memory.  Waits for the index's searches in flight.

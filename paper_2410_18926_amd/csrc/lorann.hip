@@ -1072,35 +1072,48 @@ int search_chunk(lorann_index* ix, Workspace& ws, hipStream_t s, const float* dQ
     return LORANN_OK;
 }
 
-// What the screened re-rank's bound keeps of this index's candidates in the current re-rank mode, from a search of 256 of its rows
-// (buffers of its own, given back; nothing is measured - and the screening taken as useful - where no such search can run).
+// What the screened re-rank's bound keeps of this index's candidates in the current re-rank mode, from a search of a few hundred of its rows
+// (a block of memory of its own, given back; nothing is measured - and the screening taken as useful - where no such search can run).
 int measure_screening(lorann_index* ix) {
     if (ix->rerank_mode == LORANN_RERANK_NONE || !ix->corpus_h) return LORANN_OK;
     float& keeps = ix->screen_keeps[ix->rerank_mode == LORANN_RERANK_F16];
     if (keeps >= 0.0f) return LORANN_OK;
-    const int count = (int)std::min<int64_t>(256, ix->n), k = 10, m = 200, w = std::min(32, (int)ix->L);
+    const int k = 10, m = 200, w = std::min(32, (int)ix->L);
+    int64_t sample = 256;
+    // (a large cluster must not be left to the one wavefront that streams it: 7.9 ms at 157 000 points)
+    if (ix->max_cluster > kWaveWholePoints && pair_max_streams(sample * w, ix->L) && (int64_t)16 * ix->L < (int64_t)2048 * w) sample = (int64_t)16 * ix->L / w + 1;
+    const int count = (int)std::min(sample, ix->n);
     if (count <= kSmallPathQueries || ix->n < 2 * m || (size_t)ix->d * 4 + 256 * 12 > 64 * 1024) return LORANN_OK;
     const std::string said = g_err;
-    const int32_t turns = ix->gather_turns, exact = ix->force_exact, screening = ix->rerank_screening;
+    const int32_t exact = ix->force_exact, screening = ix->rerank_screening;
     const bool prof = ix->prof_on;
-    ix->gather_turns = 0; ix->force_exact = 0; ix->prof_on = false; ix->rerank_screening = LORANN_RERANK_SCREEN_ALWAYS;
+    ix->force_exact = 0; ix->prof_on = false; ix->rerank_screening = LORANN_RERANK_SCREEN_ALWAYS;
+    // one allocation: the search's buffers as slices of it, the queries, the counts and the results behind them
     Workspace ws;
-    DevBuf q, ids, dists;
+    Arena arena;
+    ws.arena = &arena;
     std::vector<int32_t> kept((size_t)count, k);
-    int rc = q.reserve((size_t)count * ix->d * 4);
-    if (rc == LORANN_OK) rc = ids.reserve((size_t)count * k * 8);
-    if (rc == LORANN_OK) rc = dists.reserve((size_t)count * k * 4);
-    if (rc == LORANN_OK) rc = ws.kept.reserve((size_t)count * 4);
-    if (rc == LORANN_OK && plan_chunk(ix, count, k, w, m).screened) {
-        hipLaunchKernelGGL(k_sample_rows, dim3((unsigned)count), dim3(256), 0, ix->stream, ix->corpus, q.as<float>(), ix->n, ix->d, count);
-        rc = search_chunk(ix, ws, ix->stream, q.as<float>(), count, k, w, m, ids.as<int64_t>(), dists.as<float>(), nullptr, 0, nullptr);
-        if (rc == LORANN_OK && (hipStreamSynchronize(ix->stream) != hipSuccess || ws.last_screened == 0 ||
-                                hipMemcpy(kept.data(), ws.kept.p, kept.size() * 4, hipMemcpyDeviceToHost) != hipSuccess)) rc = LORANN_E_DEVICE;
+    const ChunkPlan pl = plan_chunk(ix, count, k, w, m, false);
+    unsigned char* block = nullptr;
+    int rc = pl.screened ? LORANN_OK : LORANN_E_UNSUPPORTED;
+    if (rc == LORANN_OK) {
+        (void)reserve_workspace(ix, ws, pl, count, w, m, false);          // (an empty region: adds up what is needed)
+        const size_t need = (arena.used + 255) & ~(size_t)255, qb = ((size_t)count * ix->d * 4 + 255) & ~(size_t)255;
+        if (hipMalloc((void**)&block, need + qb + (size_t)count * (k * 12 + 4)) != hipSuccess) rc = LORANN_E_NOMEM;
+        else {
+            arena.base = block; arena.cap = need;
+            float* q = reinterpret_cast<float*>(block + need);
+            int64_t* ids = reinterpret_cast<int64_t*>(block + need + qb);
+            float* dists = reinterpret_cast<float*>(ids + (size_t)count * k);
+            ws.kept.p = dists + (size_t)count * k;
+            hipLaunchKernelGGL(k_sample_rows, dim3((unsigned)count), dim3(256), 0, ix->stream, ix->corpus, q, ix->n, ix->d, count);
+            rc = search_chunk(ix, ws, ix->stream, q, count, k, w, m, ids, dists, nullptr, 0, nullptr);
+            if (hipStreamSynchronize(ix->stream) != hipSuccess) rc = LORANN_E_DEVICE;
+            if (rc == LORANN_OK && (ws.last_screened == 0 || hipMemcpy(kept.data(), ws.kept.p, kept.size() * 4, hipMemcpyDeviceToHost) != hipSuccess)) rc = LORANN_E_DEVICE;
+        }
     }
-    ix->gather_turns = turns; ix->force_exact = exact; ix->prof_on = prof; ix->rerank_screening = screening;
-    DevBuf* bufs[] = {&q, &ids, &dists};
-    for (DevBuf* b : bufs) b->release();
-    ws.release();
+    ix->force_exact = exact; ix->prof_on = prof; ix->rerank_screening = screening;
+    if (block) (void)hipFree(block);
     if (rc != LORANN_OK) { g_err = said; (void)hipGetLastError(); return LORANN_OK; }
     double beyond = 0.0;
     for (int32_t c : kept) beyond += std::max(0, c - k);
