@@ -170,21 +170,19 @@ __global__ __launch_bounds__(256) void k_select_wave(QuerySelectArgs a) {
         exact = at_lo == m;
         return lo;
     };
-    // Smallest row with at least `need` of the list's entries of key K in rows up to it.
-    auto row_of_ties = [&](uint32_t K, int need) {
-        uint32_t lo = 0u, hi = 0x7fffffffu;
-        while (lo < hi) {                        // uniform
-            const uint32_t mid = lo + ((hi - lo) >> 1);
-            int c = 0;
-            for (int i0 = 0; i0 < n; i0 += 64) c += __popcll(__ballot(i0 + lane < n && keys[i0 + lane] == K && (uint32_t)rows[i0 + lane] <= mid));
-            if (c >= need) hi = mid; else lo = mid + 1u;
-        }
-        return lo;
-    };
     auto load_keys = [&](uint32_t (&ek)[EPL]) {
         lds_sync();
 #pragma unroll
         for (int e = 0; e < EPL; ++e) ek[e] = 64 * e + lane < n ? keys[64 * e + lane] : 0u;
+    };
+    // Smallest row up to which at least `need` entries count; entries(mid): how many do up to row `mid`.
+    auto row_of_ties = [&](int need, auto entries) {
+        uint32_t lo = 0u, hi = 0x7fffffffu;
+        while (lo < hi) {                        // uniform
+            const uint32_t mid = lo + ((hi - lo) >> 1);
+            if (entries(mid) >= need) hi = mid; else lo = mid + 1u;
+        }
+        return lo;
     };
 
     constexpr bool INT = !L2 && !EXT;           // one scale per pair, no bias: integer scores are compared, and converted once accepted
@@ -239,18 +237,22 @@ __global__ __launch_bounds__(256) void k_select_wave(QuerySelectArgs a) {
             convert();
             bin = read_bins();
             thin_out();
-            if (n > LIMIT) {                             // one bin holds too many: the m best (m <= LIMIT - 96), ties to the lower rows
+            if (n > LIMIT) {                             // one bin holds too many: the m best exactly (m <= LIMIT - 96)
                 uint32_t ek[EPL];
                 load_keys(ek);
                 bool exact;
                 T = mth_largest(ek, max(T, 1u), 0xffffffffu, exact);
-                if (!exact) {
-                    int above = 0;
-#pragma unroll
-                    for (int e = 0; e < EPL; ++e) above += __popcll(__ballot(ek[e] > T));
-                    R_tie = row_of_ties(T, m - above);
-                    T_tie = T;
-                }
+                thin_out();
+            }
+            if (n > LIMIT) {                             // too many tie with the m-th: those in the lowest rows (over the list in LDS: rare)
+                auto entries = [&](auto f) {
+                    int c = 0;
+                    for (int i0 = 0; i0 < n; i0 += 64) c += __popcll(__ballot(i0 + lane < n && f(i0 + lane)));
+                    return c;
+                };
+                const int above = entries([&](int i) { return keys[i] > T; });
+                R_tie = row_of_ties(m - above, [&](uint32_t mid) { return entries([&](int i) { return keys[i] == T && (uint32_t)rows[i] <= mid; }); });
+                T_tie = T;
                 thin_out();
             }
             n_keys = n;
@@ -373,15 +375,22 @@ __global__ __launch_bounds__(256) void k_select_wave(QuerySelectArgs a) {
     }
     // entries above K, and of those equal to it the ones in the lowest rows
     uint32_t R = 0xffffffffu;
+    int32_t er[EPL];
+#pragma unroll
+    for (int e = 0; e < EPL; ++e) er[e] = 64 * e + lane < n ? rows[64 * e + lane] : 0x7fffffff;
     if (!exact) {
         int above = 0;
 #pragma unroll
         for (int e = 0; e < EPL; ++e) above += __popcll(__ballot(ek[e] > K));
-        R = row_of_ties(K, m - above);                   // 1 <= m - above < the entries equal to K
-    }
-    int32_t er[EPL];
+        // 1 <= m - above < the entries equal to K.  (Rows in registers: one query in a hundred gets here, bisecting over LDS took it 13 us,
+        // and the kernel lasts as long as its slowest query: 10 000 queries of the 768-d workload 68 us against 53.)
+        R = row_of_ties(m - above, [&](uint32_t mid) {
+            int c = 0;
 #pragma unroll
-    for (int e = 0; e < EPL; ++e) er[e] = 64 * e + lane < n ? rows[64 * e + lane] : 0x7fffffff;
+            for (int e = 0; e < EPL; ++e) c += __popcll(__ballot(ek[e] == K && (uint32_t)er[e] <= mid));
+            return c;
+        });
+    }
     int at0 = 0, mn = 0x7fffffff;
 #pragma unroll
     for (int e = 0; e < EPL; ++e) {
