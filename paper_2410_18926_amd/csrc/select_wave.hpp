@@ -113,6 +113,7 @@ __global__ __launch_bounds__(256) void k_select_wave(QuerySelectArgs a) {
     float Tf = -INFINITY;     // the same as a score
     int n = 0, n_keys = 0;    // entries in the list, those of them that are keys (uniform)
     uint32_t T_tie = 0u, R_tie = 0u;      // m of the entries seen beat every later one of key T_tie in a row beyond R_tie
+    bool strict = false;      // so no later point of this cluster can win a tie with T: scores have to exceed it
     const unsigned long long below = (1ull << lane) - 1ull;
 
     auto read_bins = [&]() {                    // T := far edge of the bin that holds the m-th best score seen (n >= m)
@@ -137,7 +138,7 @@ __global__ __launch_bounds__(256) void k_select_wave(QuerySelectArgs a) {
         if (t > T) T = t;
         return bin;
     };
-    auto set_threshold = [&]() { Tf = T > 0x007fffffu ? key_to_float(T) : -INFINITY; };
+    auto set_threshold = [&]() { Tf = T > 0x007fffffu ? key_to_float(strict ? T + 1u : T) : -INFINITY; };
     auto thin_out = [&]() {                     // keep the entries >= T, of those equal to T the ones that can still count (stable, in place)
         lds_sync();
         const uint32_t R = T == T_tie ? R_tie : 0x7fffffffu;
@@ -175,9 +176,8 @@ __global__ __launch_bounds__(256) void k_select_wave(QuerySelectArgs a) {
 #pragma unroll
         for (int e = 0; e < EPL; ++e) ek[e] = 64 * e + lane < n ? keys[64 * e + lane] : 0u;
     };
-    // Smallest row up to which at least `need` entries count; entries(mid): how many do up to row `mid`.
-    auto row_of_ties = [&](int need, auto entries) {
-        uint32_t lo = 0u, hi = 0x7fffffffu;
+    // Smallest row in [lo, hi] up to which at least `need` entries count; entries(mid): how many do up to row `mid`.
+    auto row_of_ties = [&](int need, uint32_t lo, uint32_t hi, auto entries) {
         while (lo < hi) {                        // uniform
             const uint32_t mid = lo + ((hi - lo) >> 1);
             if (entries(mid) >= need) hi = mid; else lo = mid + 1u;
@@ -231,9 +231,11 @@ __global__ __launch_bounds__(256) void k_select_wave(QuerySelectArgs a) {
             if (!(sp > 0.0f)) { yT = 0.0f >= Tf ? (int)0x80000000 : 0x7fffffff; return; }
             const float t = Tf / sp;
             yT = (int)fminf(fmaxf(floorf(t - 1e-6f * fabsf(t)) - 1.0f, -1.0e9f), 1.0e9f);
+            if (strict) for (int i = 0; i < 3 && __fmaf_rn((float)yT, sp, -0.0f) < Tf; ++i) ++yT;      // the tied score itself
         };
+        if (strict) { strict = false; set_threshold(); }
         int_threshold();
-        auto make_room = [&]() {                         // the list is nearly full
+        auto make_room = [&](int row0) {                 // the list is nearly full; no later point of the cluster has a row below row0
             convert();
             bin = read_bins();
             thin_out();
@@ -241,7 +243,7 @@ __global__ __launch_bounds__(256) void k_select_wave(QuerySelectArgs a) {
                 uint32_t ek[EPL];
                 load_keys(ek);
                 bool exact;
-                T = mth_largest(ek, max(T, 1u), 0xffffffffu, exact);
+                T = mth_largest(ek, max(T, 1u), max(bin == 0 ? 0xffffffffu : kmax - wave_bin_first(bin) + 1u, T + 1u), exact);      // (as in the final selection)
                 thin_out();
             }
             if (n > LIMIT) {                             // too many tie with the m-th: those in the lowest rows (over the list in LDS: rare)
@@ -250,20 +252,24 @@ __global__ __launch_bounds__(256) void k_select_wave(QuerySelectArgs a) {
                     for (int i0 = 0; i0 < n; i0 += 64) c += __popcll(__ballot(i0 + lane < n && f(i0 + lane)));
                     return c;
                 };
+                uint32_t first = 0x7fffffffu, last = 0u;
+                for (int i = lane; i < n; i += 64) if (keys[i] == T) { first = min(first, (uint32_t)rows[i]); last = max(last, (uint32_t)rows[i]); }
                 const int above = entries([&](int i) { return keys[i] > T; });
-                R_tie = row_of_ties(m - above, [&](uint32_t mid) { return entries([&](int i) { return keys[i] == T && (uint32_t)rows[i] <= mid; }); });
+                R_tie = row_of_ties(m - above, wave_min_u32(first), ~wave_min_u32(~last), [&](uint32_t mid) { return entries([&](int i) { return keys[i] == T && (uint32_t)rows[i] <= mid; }); });
                 T_tie = T;
                 thin_out();
             }
+            strict = T == T_tie && R_tie < (uint32_t)row0;
             n_keys = n;
             set_threshold();
             int_threshold();
             n_read = n;
         };
+        const bool large = a.sub && m_c > kSubMinPoints;  // uniform: looked into by quarters if it has them
         // one piece of up to 64 points: this lane's is point base + own
         int z[ZW];                                       // uniform: scalar registers
         auto score = [&](const Piece& pc, int own, int base) {
-            if (n > LIMIT) make_room();
+            if (n > LIMIT) make_room(r0 + (large ? base & ~(kChunkPoints - 1) : base));      // (quarters: rows ascend from chunk to chunk)
             int y = 0;
 #pragma unroll
             for (int u = 0; u < RB; ++u)
@@ -292,7 +298,7 @@ __global__ __launch_bounds__(256) void k_select_wave(QuerySelectArgs a) {
         int nq4 = 0;                                     // quarters of a large cluster
         const uint32_t* subp = nullptr;
         size_t sub_step = 0;
-        if (a.sub && m_c > kSubMinPoints) {              // uniform
+        if (large) {
             const int c = __builtin_amdgcn_readfirstlane(a.sel[(size_t)q * w + jp]), pos = __builtin_amdgcn_readfirstlane(ppos[jp]);
             const int at = pos - a.bucket_off[c], first = a.sub_first[c], chunks = (m_c + kChunkPoints - 1) / kChunkPoints;
             if (first + chunks <= a.sub_chunks) {
@@ -384,7 +390,7 @@ __global__ __launch_bounds__(256) void k_select_wave(QuerySelectArgs a) {
         for (int e = 0; e < EPL; ++e) above += __popcll(__ballot(ek[e] > K));
         // 1 <= m - above < the entries equal to K.  (Rows in registers: one query in a hundred gets here, bisecting over LDS took it 13 us,
         // and the kernel lasts as long as its slowest query: 10 000 queries of the 768-d workload 68 us against 53.)
-        R = row_of_ties(m - above, [&](uint32_t mid) {
+        R = row_of_ties(m - above, 0u, 0x7fffffffu, [&](uint32_t mid) {
             int c = 0;
 #pragma unroll
             for (int e = 0; e < EPL; ++e) c += __popcll(__ballot(ek[e] == K && (uint32_t)er[e] <= mid));
