@@ -441,7 +441,8 @@ ChunkPlan plan_chunk(const lorann_index* ix, int64_t nq, int k, int w, int m, bo
     pl.handful = pl.small && pl.grouped && nq <= 8 && ix->d % 4 == 0 && ix->d <= 1024 && k <= 64;
     // The screened re-rank reads all candidates at half width and about k of them in full: it pays while those are a small part of m
     // (a row read at half width is shared by about two queries, one read in full is not).  A few dozen queries are
-    // bound by the latency of the three launches, where the grouped re-rank's are shorter (64 queries: 115 us against 118).
+    // bound by the latency of the three launches, where the grouped re-rank's are shorter (64 queries: 115 us against 118; 2 queries with
+    // column-wise step sizes, which take the batched kernels before it: 85 against 92).
     const int ld = half_stride(ix->d);
     pl.screen_gq = std::min(pl.small ? 1 : screen_group_size(m), (64 * 1024) / (2 * ld + 16));
     // With few queries per cluster (nq <= 2 L) the queries of a group hardly share rows: 16 of them fill the union's table to 0.8 with
@@ -450,7 +451,7 @@ ChunkPlan plan_chunk(const lorann_index* ix, int64_t nq, int k, int w, int m, bo
     // 4096; 1024 over 1024 42 -> 17, 59 -> 61.  Not beyond: 1000 queries over 64 clusters 14 -> 12, but 10 -> 13 for twice the rows;
     // 16 384 queries over 16 384 clusters in groups of 4 lose (51 -> 69).
     if (!pl.small && nq <= 2 * (int64_t)L) pl.screen_gq = (int)std::min<int64_t>(pl.screen_gq, std::max<int64_t>(4, (nq + 1023) / 1024));
-    pl.screened = allow_screened && ix->rerank_mode != LORANN_RERANK_NONE && !ix->force_exact && !(pl.small && pl.grouped) && ix->corpus_h && pl.screen_gq > 0 && 4 * k <= m &&
+    pl.screened = allow_screened && ix->rerank_mode != LORANN_RERANK_NONE && !ix->force_exact && !(nq <= kSmallPathQueries && pl.grouped) && ix->corpus_h && pl.screen_gq > 0 && 4 * k <= m &&
                   (ix->rerank_screening == LORANN_RERANK_SCREEN_ALWAYS || (ix->rerank_screening == LORANN_RERANK_SCREEN_AUTO && screening_pays(ix, k, m, pl.grouped)));
     pl.screen_stride = (pl.screen_gq * m + 15) & ~15;
     if (pl.screened) pl.grouped = false;

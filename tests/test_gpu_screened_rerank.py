@@ -248,3 +248,22 @@ def test_the_half_precision_copy_is_given_back(B):
     with pytest.raises(B.LorannError):
         gix.set_rerank_screening(3)
     gix.close()
+
+
+@pytest.mark.parametrize("nq,screened", [(2, False), (64, False), (65, True)])
+def test_a_few_dozen_queries_share_full_rows(B, nq, screened):
+    """Whatever the kernels in front of it - column-wise step sizes take the batched ones at any size - up to 64 queries are not screened."""
+    rng = np.random.default_rng(nq)
+    ix = _random_index(rng, n=5000, d=64, L=6, r=8, metric=0, dp=32)
+    ix["scale_A_columns"] = rng.uniform(0.01, 0.1, (6, 8)).astype(np.float32)
+    ix["scale_B_points"] = rng.uniform(0.01, 0.1, 5000).astype(np.float32)
+    q = rng.normal(size=(nq, 64)).astype(np.float32)
+    gix = B.Index(**ix)
+    gix.set_rerank_screening(B.RERANK_SCREEN_ALWAYS)
+    ids, d = gix.search(q, 10, 4, 100)
+    assert gix.profile_gather_plan()[1] == screened
+    gix.set_exact_selection(True)
+    e_ids, e_d = gix.search(q, 10, 4, 100)
+    gix.close()
+    np.testing.assert_array_equal(ids, e_ids)
+    np.testing.assert_array_equal(d, e_d)
